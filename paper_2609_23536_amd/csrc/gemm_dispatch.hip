@@ -1,0 +1,146 @@
+// Tile choice of the FP8 GEMM.
+#include "gemm_util.h"
+
+#include <atomic>
+
+namespace qe {
+
+// What a product costs with each tile shape, in microseconds, fitted to a
+// sweep of 33 products on MI355X (M 64 to 14336, N 152 to 28672, K 128 to
+// 19456, BF16 / FP32 / accumulate outputs; the shape it picks is 3% slower on
+// average than the best one of each product).
+//
+// Large tiles run one workgroup per compute unit, round after round: a round
+// of 256 x 256 tiles costs F + T * s, with T = K tiles of 128, s = 1.0 on a
+// chip at most a quarter full and 1.2 beyond (measured: K = 14336 on 32 tiles
+// 118, on 128 tiles 136), and F the prologue and the epilogue's burst of output
+// traffic, by output type (FP32: 4096 x 4096 x 256, 18 in all; an accumulation
+// moves twice the bytes, and more than one round of it also waits for the
+// write-back of the one before).  The narrower tiles' rounds, relative to
+// 256 x 256 (K = 4096, one round of each, BF16 out): 256 x 192 0.89,
+// 192 x 256 0.86 (0.75 of the MFMA work at a lower efficiency per FLOP),
+// 256 x 224 0.978.
+constexpr double kLargeF[3] = {14.0, 9.0, 25.0};  // by GemmParams::out: FP32, BF16, accumulate
+constexpr double kLargeF2 = 28.0;                 // accumulate, more than one round
+// added to F where rows are not vector-aligned: the checked epilogue's single
+// elements (2730 x 1365 x 1000: FP32 34, accumulate 78)
+constexpr double kLargeScalar[3] = {12.0, 12.0, 42.0};
+constexpr double kCost256x192 = 0.89;
+constexpr double kCost192x256 = 0.86;
+constexpr double kCost224 = 0.98;
+
+// Small tiles cost F + c * (T * s + E), c being the tiles of the busiest
+// compute unit: their K loops are bound by the LDS-bound loads (about 84 bytes
+// per ns and compute unit), so s does not depend on how many workgroups share
+// the unit, and E is the epilogue's traffic that the other workgroup's K loop
+// does not hide.  s grows with K as the operands outgrow the caches (128 x 128,
+// two tiles per unit: K = 8192 57, K = 14336 127).  `scalar` is added to E where
+// rows are not vector-aligned.
+struct SmallTile {
+  int tile, deep;  // deep: the variant for grids of one workgroup per unit (0: none)
+  int64_t bm, bn;
+  double f, s, s_k, s_deep, e[3], scalar;  // s + s_k * T per K tile
+};
+constexpr SmallTile kSmall[] = {
+    {kTile64x64, 0, 64, 64, 3.0, 0.19, 0.0, 0.0, {0.6, 0.3, 1.2}, 1.2},
+    {kTile128x64, kTile128x64Deep, 128, 64, 3.5, 0.30, 0.0, 0.295, {1.2, 0.5, 2.4}, 2.4},
+    {kTile64x128, kTile64x128Deep, 64, 128, 3.5, 0.30, 0.0, 0.295, {1.2, 0.5, 2.4}, 2.4},
+    {kTile128x128, kTile128x128Deep, 128, 128, 4.0, 0.46, 0.0008, 0.52, {2.2, 0.6, 5.6}, 4.8},
+};
+
+static std::atomic<int> g_tile_override{0};
+
+// Compute units of the current device, read once per device from its properties; 256 on MI355X.
+static int cu_count() {
+  constexpr int kMaxDevices = 64;
+  static std::atomic<int> cache[kMaxDevices];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
+  int n = cache[dev].load(std::memory_order_relaxed);
+  if (n > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+  cache[dev].store(n, std::memory_order_relaxed);
+  return n;
+}
+
+hipError_t launch_gemm(const GemmParams &g, hipStream_t s, const UpdateParams *fused) {
+  UpdateParams none;
+  memset(&none, 0, sizeof(none));
+  const UpdateParams &u = fused != nullptr ? *fused : none;
+  if (g.m <= 0 || g.n <= 0) return u.n > 0 ? launch_scale_update(u, s) : hipSuccess;
+  // The kernel addresses each operand with 32-bit offsets: split any operand
+  // of 2 GiB or more into row blocks (independent GEMMs on disjoint outputs),
+  // whole 256-row tiles per block where a tile's rows fit in 2 GiB, else as
+  // many rows as fit (at least one: its offsets are then 0 plus the K offset,
+  // which stays below 2^31 because K does).
+  constexpr int64_t kLim = int64_t(1) << 31;
+  if (g.k >= kLim) return hipErrorInvalidValue;
+  auto block_rows = [](int64_t ld) -> int64_t {
+    const int64_t r = (kLim - 1) / ld;
+    return r >= 256 ? r / 256 * 256 : (r > 0 ? r : 1);
+  };
+  const int64_t cbytes = g.out == 1 ? 2 : 4;
+  if (g.m * g.lda >= kLim) {
+    const int64_t rows = block_rows(g.lda);
+    for (int64_t r = 0; r < g.m; r += rows) {
+      GemmParams sub = g;
+      sub.a = g.a + r * g.lda;
+      sub.m = g.m - r < rows ? g.m - r : rows;
+      sub.c = static_cast<char *>(g.c) + r * g.ldc * cbytes;
+      const hipError_t e = launch_gemm(sub, s, r + rows >= g.m ? fused : nullptr);  // the update rides on the last
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  if (g.n * g.ldb >= kLim) {
+    const int64_t cols = block_rows(g.ldb);
+    for (int64_t c0 = 0; c0 < g.n; c0 += cols) {
+      GemmParams sub = g;
+      sub.b = g.b + c0 * g.ldb;
+      sub.n = g.n - c0 < cols ? g.n - c0 : cols;
+      sub.c = static_cast<char *>(g.c) + c0 * cbytes;
+      const hipError_t e = launch_gemm(sub, s, c0 + cols >= g.n ? fused : nullptr);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  const int force = g_tile_override.load(std::memory_order_relaxed);
+  if (force == kTile256x128 || force >= kTile64x64) return launch_gemm_ring(force, g, s, u);
+  if (force > 0) return launch_gemm_large(force, g, s, u);
+  const int64_t cus = cu_count();
+  const double T = double((g.k + 127) / 128);
+  auto tiles = [&](int64_t bm, int64_t bn) { return ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn); };
+  const bool scalar = !gemm_vec_ok(g);
+  double best = 0.0;
+  int pick = 0;
+  auto offer = [&](int tile, double cost) {
+    if (pick == 0 || cost < best) {
+      best = cost;
+      pick = tile;
+    }
+  };
+  // Large tiles: the narrower ones win where the 256 x 256 grid leaves its
+  // last round mostly empty (N = 6144: 384 tiles = 1.5 rounds, against 512
+  // tiles of 256 x 192 = 2 rounds of 0.89; N = 14336: 896 tiles = 3.5 rounds,
+  // against 1024 of 256 x 224 = 4 of 0.98).
+  auto large = [&](int tile, int64_t bm, int64_t bn, double rel) {
+    const int64_t n = tiles(bm, bn), rounds = (n + cus - 1) / cus;
+    const double f = (g.out == 2 && rounds > 1 ? kLargeF2 : kLargeF[g.out]) + (scalar ? kLargeScalar[g.out] : 0.0);
+    offer(tile, rel * double(rounds) * (f + T * (4 * n <= cus ? 1.0 : 1.2)));
+  };
+  large(kTile256x256, 256, 256, 1.0);
+  large(kTile256x224, 256, 224, kCost224);
+  large(kTile256x192, 256, 192, kCost256x192);
+  large(kTile192x256, 192, 256, kCost192x256);
+  for (const SmallTile &t : kSmall) {
+    const int64_t c = (tiles(t.bm, t.bn) + cus - 1) / cus;
+    const bool deep = t.deep != 0 && c == 1;
+    offer(deep ? t.deep : t.tile,
+          t.f + double(c) * (T * (deep ? t.s_deep : t.s + t.s_k * T) + t.e[g.out] + (scalar ? t.scalar : 0.0)));
+  }
+  return pick >= kTile64x64 ? launch_gemm_ring(pick, g, s, u) : launch_gemm_large(pick, g, s, u);
+}
+
+void set_gemm_tile_override(int tile) { g_tile_override.store(tile, std::memory_order_relaxed); }
+
+}  // namespace qe

@@ -10,25 +10,21 @@
 // it to an FP32 destination in place: the direct placement of dW into its
 // slice of the flat main-gradient buffer (§3.4), with no staging copy.
 //
-// Two kernels share the scheme below; both use v_mfma_f32_16x16x128_f8f6f4
-// with the same assignment of reduction bytes to lanes, so every tile shape
-// accumulates each output element in the same order and gives the same bits.
-//  * gemm_tn_w4_kernel, 256 x 256 x 128 tiles (and 256 x 224, 256 x 192,
-//    192 x 256): four waves (one per SIMD) on a 2 x 2 grid, each a 128 x 128 sub-tile of
-//    8 x 8 MFMA blocks.  A K tile's 64 MFMAs run in two phases; every fragment
-//    read or LDS-bound load is issued right after an MFMA, in a fixed order
-//    (sched_barrier), so the MFMA pipe stays busy in the single wave, and the
-//    LDS-bound loads are branch-free (two instructions each) because a single
-//    wave issues at most one instruction per four cycles, eight per MFMA.
-//    The K loop is rotated so that its back-edge sits at the stage barrier,
-//    where all LDS reads have completed; the compiler can then wait for
-//    fragment reads one by one instead of draining them at the loop head.
-//    The epilogue goes through LDS so every store instruction writes whole
-//    row runs (512-byte FP32 runs; BF16 values are rounded first and go as
-//    256-byte runs).  Larger wave tiles mean less LDS traffic per FLOP than
-//    eight waves.
-//  * gemm_tn_kernel, 256 x 128 x 128 tiles: eight waves (two per SIMD) on a
-//    4 x 2 grid; used when it quantizes better onto the compute units.
+// gemm_tn_w4_kernel serves the large tiles, 256 x 256 x 128 (and 256 x 224,
+// 256 x 192, 192 x 256); gemm_ring.hip the small ones.  Every shape uses
+// v_mfma_f32_16x16x128_f8f6f4 with the same assignment of reduction bytes to
+// lanes and accumulates each output element in the same order, so all give the
+// same bits.  Four waves (one per SIMD) on a 2 x 2 grid, each a 128 x 128
+// sub-tile of 8 x 8 MFMA blocks.  A K tile's 64 MFMAs run in two phases; every
+// fragment read or LDS-bound load is issued right after an MFMA, in a fixed
+// order (sched_barrier), so the MFMA pipe stays busy in the single wave, and
+// the LDS-bound loads are branch-free (two instructions each) because a single
+// wave issues at most one instruction per four cycles, eight per MFMA.  The K
+// loop is rotated so that its back-edge sits at the stage barrier, where all
+// LDS reads have completed; the compiler can then wait for fragment reads one
+// by one instead of draining them at the loop head.  The epilogue goes through
+// LDS so every store instruction writes whole row runs (512-byte FP32 runs;
+// BF16 values are rounded first and go as 256-byte runs).
 // Operand formats (E4M3 or E5M2) are chosen per call.  K tiles are
 // double-buffered in LDS and filled by LDS-bound global loads
 // (global_load_lds_dwordx4: no register staging, no LDS store instructions)
@@ -57,292 +53,11 @@
 //
 // Determinism: no atomics and no split reduction; the same inputs produce the
 // same bits, which the split-vs-full-backward check relies on.
-#include "kernels.h"
+#include "gemm_util.h"
 #include "scale_update.h"
-
-#include <atomic>
 
 namespace qe {
 namespace {
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-constexpr int BK = 128;
-// Tiles are numbered down groups of kGroupM row tiles, column after column,
-// and each XCD takes a contiguous range of that order, so a round's 32 tiles
-// on one XCD are 4 row tiles x 8 column tiles sharing their operand slabs in
-// its L2.  Measured on MI355X over the Llama-3-70B stage's twelve products:
-// 4 rows 1.2% faster than 8 (two runs), 2 rows 1.8% slower, 16 rows 5%
-// slower; the 8B stage's products are level between 4, 6 and 8.
-constexpr int kGroupM = 4;
-
-
-// Cache policy of the epilogue's output traffic (stores, and the destination
-// reads of the accumulate mode): non-temporal.  The output is written once
-// and not read again by this kernel, so keeping it out of the L2 leaves the L2
-// to the operand rows and columns that later tiles of the grid re-read;
-// measured on MI355X over the Llama-3-8B stage's twelve products: -3.7% time
-// with FP32 / BF16 stores, -5% in accumulate mode, most on the seven-round
-// shapes.
-constexpr int kNT = 2;  // the buffer instructions' nt bit
-
-__device__ __forceinline__ uint32_t lds_off(int row, int chunk) {
-  return uint32_t(row) * BK + (uint32_t((chunk ^ (row >> 1)) & 7) << 4);
-}
-
-__device__ __forceinline__ uint4 mask_tail(uint4 v, int64_t valid) {
-  // keep bytes [0, valid), zero the rest; branch-free
-  uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int64_t nb = valid - 4 * q;  // bytes of this dword to keep
-    const int k = nb <= 0 ? 0 : (nb >= 4 ? 4 : int(nb));
-    w[q] &= uint32_t((uint64_t(1) << (8 * k)) - 1u);
-  }
-  return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-// Two floats to two bf16 (round to nearest even, NaN stays a quiet NaN with
-// its sign and top payload bits) with the gfx950 packed conversion; bit-equal
-// to the integer form (u + 0x7fff + ((u >> 16) & 1)) >> 16 on every input,
-// which was checked on MI355X over all exponents, boundaries, denormals and NaNs.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t bf16x2_bits(float lo, float hi) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
-}
-__device__ __forceinline__ uint16_t bf16_bits(float f) { return uint16_t(bf16x2_bits(f, 0.0f)); }
-
-__device__ __forceinline__ int pow2_exponent(const float *p) { return int((__float_as_uint(*p) >> 23) & 0xffu) - 127; }
-
-// Workgroups are dealt to the 8 XCDs round-robin; renumber so that each XCD
-// gets a contiguous range of tiles (shared A rows / B columns stay in one L2).
-__device__ __forceinline__ int xcd_remap(int wg, int total) {
-  const int per = total / 8, rem = total % 8;
-  const int xcd = wg % 8, idx = wg / 8;
-  return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
-}
-
-template <int BM, int BN, int WM, int WN, int FA, int FB, int OUT>
-__global__ __launch_bounds__(WM *WN * 64) void gemm_tn_kernel(GemmParams g, int tiles_m, int tiles_n, int vec_ok) {
-  constexpr int NT = WM * WN * 64;
-  constexpr int TM = BM / WM, TN = BN / WN;
-  constexpr int FI = TM / 16, FJ = TN / 16;
-  constexpr int ACH = BM * (BK / 16) / NT;
-  constexpr int BCH = BN * (BK / 16) / NT;
-  static_assert(ACH * NT == BM * (BK / 16) && BCH * NT == BN * (BK / 16), "tile / thread mismatch");
-
-  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * (BM + BN) * BK];
-  constexpr int NW = WM * WN;
-  constexpr int STAGE = (BM + BN) * BK;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-
-  const int pid = xcd_remap(blockIdx.x, tiles_m * tiles_n);
-  const int in_group = kGroupM * tiles_n;
-  const int group = pid / in_group;
-  const int first_m = group * kGroupM;
-  const int gsize = min(tiles_m - first_m, kGroupM);
-  const int tm = first_m + (pid % in_group) % gsize;
-  const int tn = (pid % in_group) / gsize;
-  const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
-
-  const int64_t M = g.m, N = g.n, K = g.k;
-  const int KT = int(K / BK);
-  const int64_t ktail = K - int64_t(KT) * BK;
-  const int T = KT + (ktail > 0 ? 1 : 0);
-
-  // LDS-bound loads: each wave instruction fills one contiguous 1 KB block
-  // (8 rows x 128 B), lane l writing bytes 16l..16l+15; lane l fetches the
-  // global chunk that the swizzle puts at row 8b + l/8, physical chunk l % 8.
-  const int lrow = lane >> 3;
-  uint32_t oa[ACH], ob[BCH];
-#pragma unroll
-  for (int c = 0; c < ACH; ++c) {
-    const int row = 8 * (wave + NW * c) + lrow;
-    const int lch = (lane & 7) ^ ((row >> 1) & 7);
-    oa[c] = uint32_t(min(m0 + row, M - 1) * g.lda) + lch * 16;
-  }
-#pragma unroll
-  for (int c = 0; c < BCH; ++c) {
-    const int row = 8 * (wave + NW * c) + lrow;
-    const int lch = (lane & 7) ^ ((row >> 1) & 7);
-    ob[c] = uint32_t(min(n0 + row, N - 1) * g.ldb) + lch * 16;
-  }
-  const uint32_t lds_base = uint32_t(reinterpret_cast<uintptr_t>(smem));
-  const uint32_t wblk = __builtin_amdgcn_readfirstlane(lds_base + uint32_t(wave) * 1024u);
-
-  v4f acc[FI][FJ];
-#pragma unroll
-  for (int i = 0; i < FI; ++i)
-#pragma unroll
-    for (int j = 0; j < FJ; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-  auto issue_full = [&](int kt, int buf) {
-    const uint8_t *ga = g.a + int64_t(kt) * BK;
-    const uint8_t *gb = g.b + int64_t(kt) * BK;
-    const uint32_t sa = wblk + uint32_t(buf * STAGE);
-    const uint32_t sb = sa + uint32_t(BM * BK);
-#pragma unroll
-    for (int c = 0; c < ACH; ++c)
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(oa[c]), "s"(ga),
-                   "s"(sa + uint32_t(c * NW * 1024)) : "memory", "m0");
-#pragma unroll
-    for (int c = 0; c < BCH; ++c)
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(ob[c]), "s"(gb),
-                   "s"(sb + uint32_t(c * NW * 1024)) : "memory", "m0");
-  };
-  auto issue_tail = [&](int buf) {
-    uint8_t *dA = smem + buf * STAGE;
-    uint8_t *dB = dA + BM * BK;
-    const uint32_t k0 = uint32_t(KT) * BK;
-#pragma unroll
-    for (int c = 0; c < ACH; ++c) {
-      const int row = 8 * (wave + NW * c) + lrow;
-      const int64_t gk = int64_t(k0) + (((lane & 7) ^ ((row >> 1) & 7)) * 16);
-      const uint4 v = gk < K ? mask_tail(*reinterpret_cast<const uint4 *>(g.a + (oa[c] + k0)), K - gk) : make_uint4(0u, 0u, 0u, 0u);
-      *reinterpret_cast<uint4 *>(dA + (wave + NW * c) * 1024 + lane * 16) = v;
-    }
-#pragma unroll
-    for (int c = 0; c < BCH; ++c) {
-      const int row = 8 * (wave + NW * c) + lrow;
-      const int64_t gk = int64_t(k0) + (((lane & 7) ^ ((row >> 1) & 7)) * 16);
-      const uint4 v = gk < K ? mask_tail(*reinterpret_cast<const uint4 *>(g.b + (ob[c] + k0)), K - gk) : make_uint4(0u, 0u, 0u, 0u);
-      *reinterpret_cast<uint4 *>(dB + (wave + NW * c) * 1024 + lane * 16) = v;
-    }
-  };
-  auto issue = [&](int t, int buf) {
-    if (t < KT)
-      issue_full(t, buf);
-    else
-      issue_tail(buf);
-  };
-
-  const int fr = lane & 15, fq = lane >> 4;
-  const uint32_t f_lo = uint32_t(fr) * BK + (uint32_t((2 * fq) ^ (fr >> 1)) & 7) * 16;
-  const uint32_t f_hi = uint32_t(fr) * BK + (uint32_t((2 * fq + 1) ^ (fr >> 1)) & 7) * 16;
-  auto frag = [&](const uint8_t *base) -> v8i {
-    const uint4 lo = *reinterpret_cast<const uint4 *>(base + f_lo);
-    const uint4 hi = *reinterpret_cast<const uint4 *>(base + f_hi);
-    return v8i{int(lo.x), int(lo.y), int(lo.z), int(lo.w), int(hi.x), int(hi.y), int(hi.z), int(hi.w)};
-  };
-
-  auto compute = [&](int buf) {
-    const uint8_t *a_s = smem + buf * STAGE + wm * TM * BK;
-    const uint8_t *b_s = smem + buf * STAGE + BM * BK + wn * TN * BK;
-    v8i bfr[FJ];
-#pragma unroll
-    for (int j = 0; j < FJ; ++j) bfr[j] = frag(b_s + j * 16 * BK);
-    v8i acur = frag(a_s);
-#pragma unroll
-    for (int i = 0; i < FI; ++i) {
-      v8i anext = acur;
-      if (i + 1 < FI) anext = frag(a_s + (i + 1) * 16 * BK);
-#pragma unroll
-      for (int j = 0; j < FJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(bfr[j], acur, acc[i][j], FB, FA, 0, 0, 0, 0);
-      acur = anext;
-    }
-  };
-
-  auto stage_sync = [&]() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-  };
-
-  if (T > 0) {
-    issue(0, 0);
-    stage_sync();
-    for (int t = 0; t < T; ++t) {
-      if (t + 1 < T) issue(t + 1, (t + 1) & 1);
-      compute(t & 1);
-      stage_sync();
-    }
-  }
-
-  // epilogue: lane holds rows (lane & 15), columns 4*(lane >> 4) .. +3 of each 16x16 block
-  const int e = pow2_exponent(g.a_scale_inv) + pow2_exponent(g.b_scale_inv);
-  const bool mfull = m0 + BM <= M, nfull = n0 + BN <= N;
-  // Full tile, vector-aligned destination: buffer stores (and accumulate
-  // loads) at a scalar block offset plus one fixed per-lane offset, with no
-  // bounds checks; every offset stays below 2^31.  Edge tiles take the checked
-  // path below.
-  constexpr int ES = OUT == 1 ? 2 : 4;  // output element bytes
-  if (vec_ok && mfull && nfull && g.ldc * ES * (BM + 1) < (int64_t(1) << 31)) {
-    const int wu = __builtin_amdgcn_readfirstlane(wave);
-    const int wmu = wu / WN, wnu = wu % WN;
-    const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
-        static_cast<char *>(g.c) + (m0 * g.ldc + n0) * ES, short(0), 0x7fffffff, 0x00020000);
-    const uint32_t voff = uint32_t((lane & 15) * g.ldc + 4 * (lane >> 4)) * uint32_t(ES);
-    const int rstep = int(g.ldc) * ES;
-#pragma unroll
-    for (int i = 0; i < FI; ++i)
-#pragma unroll
-      for (int j = 0; j < FJ; ++j) {
-        const int so = (wmu * TM + i * 16) * rstep + (wnu * TN + j * 16) * ES;
-        float v[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = __builtin_ldexpf(acc[i][j][t], e);
-        if constexpr (OUT == 0) {
-          const v4i w = {__builtin_bit_cast(int, v[0]), __builtin_bit_cast(int, v[1]), __builtin_bit_cast(int, v[2]),
-                         __builtin_bit_cast(int, v[3])};
-          __builtin_amdgcn_raw_buffer_store_b128(w, crs, voff, so, kNT);
-        } else if constexpr (OUT == 1) {
-          const v2i w = {int(bf16x2_bits(v[0], v[1])), int(bf16x2_bits(v[2], v[3]))};
-          __builtin_amdgcn_raw_buffer_store_b64(w, crs, voff, so, kNT);
-        } else {
-          const float4 o = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(crs, voff, so, kNT));
-          const float4 r = make_float4(o.x + v[0], o.y + v[1], o.z + v[2], o.w + v[3]);
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, r), crs, voff, so, kNT);
-        }
-      }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < FI; ++i) {
-    const int64_t row = m0 + wm * TM + i * 16 + (lane & 15);
-    if (!(mfull || row < M)) continue;
-#pragma unroll
-    for (int j = 0; j < FJ; ++j) {
-      const int64_t col = n0 + wn * TN + j * 16 + 4 * (lane >> 4);
-      float v[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) v[t] = __builtin_ldexpf(acc[i][j][t], e);
-      if (vec_ok && (nfull || col + 4 <= N)) {
-        if constexpr (OUT == 0) {
-          *reinterpret_cast<float4 *>(static_cast<float *>(g.c) + row * g.ldc + col) = make_float4(v[0], v[1], v[2], v[3]);
-        } else if constexpr (OUT == 1) {
-          const uint32_t lo = bf16x2_bits(v[0], v[1]);
-          const uint32_t hi = bf16x2_bits(v[2], v[3]);
-          *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(g.c) + row * g.ldc + col) = make_uint2(lo, hi);
-        } else {
-          float4 *dst = reinterpret_cast<float4 *>(static_cast<float *>(g.c) + row * g.ldc + col);
-          const float4 o = *dst;
-          *dst = make_float4(o.x + v[0], o.y + v[1], o.z + v[2], o.w + v[3]);
-        }
-      } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          if (col + t >= N) break;
-          if constexpr (OUT == 0) {
-            static_cast<float *>(g.c)[row * g.ldc + col + t] = v[t];
-          } else if constexpr (OUT == 1) {
-            static_cast<uint16_t *>(g.c)[row * g.ldc + col + t] = bf16_bits(v[t]);
-          } else {
-            float *dst = static_cast<float *>(g.c) + row * g.ldc + col + t;
-            *dst = *dst + v[t];
-          }
-        }
-      }
-    }
-  }
-}
 
 // 256 x 256 x 128 tile (also 256 x 224, 256 x 192 and 192 x 256), four waves
 // (one per SIMD) on a 2 x 2 grid, each wave a TM x TN sub-tile of 16 x 16 blocks of
@@ -774,8 +489,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
 template <int FA, int FB, int BM, int BN>
 hipError_t launch_w4(const GemmParams &g, hipStream_t s, const UpdateParams &u) {
   const int tiles_m = int((g.m + BM - 1) / BM), tiles_n = int((g.n + BN - 1) / BN);
-  const uintptr_t cp = reinterpret_cast<uintptr_t>(g.c);
-  const int vec_ok = (g.out == 1) ? (g.ldc % 4 == 0 && cp % 8 == 0) : (g.ldc % 4 == 0 && cp % 16 == 0);
+  const int vec_ok = gemm_vec_ok(g);
   const dim3 grid(unsigned(tiles_m) * unsigned(tiles_n) + unsigned(u.n)), block(256);
   switch (g.out) {
     case 0: return klaunch(gemm_tn_w4_kernel<FA, FB, 0, BM, BN>, grid, block, 0, s, g, tiles_m, tiles_n, vec_ok, u);
@@ -792,135 +506,15 @@ hipError_t launch_w4_fmts(const GemmParams &g, hipStream_t s, const UpdateParams
   return launch_w4<1, 1, BM, BN>(g, s, u);
 }
 
-template <int BM, int BN, int WM, int WN, int FA, int FB>
-hipError_t launch_out(const GemmParams &g, hipStream_t s) {
-  const int tiles_m = int((g.m + BM - 1) / BM), tiles_n = int((g.n + BN - 1) / BN);
-  const uintptr_t cp = reinterpret_cast<uintptr_t>(g.c);
-  const int vec_ok = (g.out == 1) ? (g.ldc % 4 == 0 && cp % 8 == 0) : (g.ldc % 4 == 0 && cp % 16 == 0);
-  const dim3 grid(unsigned(tiles_m) * unsigned(tiles_n)), block(WM * WN * 64);
-  switch (g.out) {
-    case 0: return klaunch(gemm_tn_kernel<BM, BN, WM, WN, FA, FB, 0>, grid, block, 0, s, g, tiles_m, tiles_n, vec_ok);
-    case 1: return klaunch(gemm_tn_kernel<BM, BN, WM, WN, FA, FB, 1>, grid, block, 0, s, g, tiles_m, tiles_n, vec_ok);
-    default: return klaunch(gemm_tn_kernel<BM, BN, WM, WN, FA, FB, 2>, grid, block, 0, s, g, tiles_m, tiles_n, vec_ok);
-  }
-}
-
-template <int BM, int BN, int WM, int WN>
-hipError_t launch_fmts(const GemmParams &g, hipStream_t s) {
-  if (g.fmt_a == 0 && g.fmt_b == 0) return launch_out<BM, BN, WM, WN, 0, 0>(g, s);
-  if (g.fmt_a == 1 && g.fmt_b == 0) return launch_out<BM, BN, WM, WN, 1, 0>(g, s);
-  if (g.fmt_a == 0 && g.fmt_b == 1) return launch_out<BM, BN, WM, WN, 0, 1>(g, s);
-  return launch_out<BM, BN, WM, WN, 1, 1>(g, s);
-}
-
 }  // namespace
 
-// Relative cost of a round of tiles against a round of 256 x 256 ones at the
-// same K, measured on MI355X (K = 4096, one round of each shape, bf16 out):
-// 256 x 192 0.89, 192 x 256 0.86 (0.75 of the MFMA work at a lower
-// efficiency per FLOP), the 8-wave 256 x 128 kernel 0.905; 256 x 224 0.978
-// (bf16 out) and 0.972 (FP32 out), two rounds against two.  Rounded up, so
-// a tie keeps the larger tile.
-constexpr double kCost192 = 0.90;
-constexpr double kCost128 = 0.92;
-constexpr double kCost224 = 0.98;
-
-static std::atomic<int> g_tile_override{0};
-
-// Compute units of the current device (one 128 KB-LDS workgroup each at a
-// time), read once per device from its properties; 256 on MI355X.
-static int cu_count() {
-  constexpr int kMaxDevices = 64;
-  static std::atomic<int> cache[kMaxDevices];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
-  int n = cache[dev].load(std::memory_order_relaxed);
-  if (n > 0) return n;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-  cache[dev].store(n, std::memory_order_relaxed);
-  return n;
-}
-
-hipError_t launch_gemm(const GemmParams &g, hipStream_t s, const UpdateParams *fused) {
-  UpdateParams none;
-  memset(&none, 0, sizeof(none));
-  const UpdateParams &u = fused != nullptr ? *fused : none;
-  if (g.m <= 0 || g.n <= 0) return u.n > 0 ? launch_scale_update(u, s) : hipSuccess;
-  // The kernel addresses each operand with 32-bit offsets: split any operand
-  // of 2 GiB or more into row blocks (independent GEMMs on disjoint outputs),
-  // whole 256-row tiles per block where a tile's rows fit in 2 GiB, else as
-  // many rows as fit (at least one: its offsets are then 0 plus the K offset,
-  // which stays below 2^31 because K does).
-  constexpr int64_t kLim = int64_t(1) << 31;
-  if (g.k >= kLim) return hipErrorInvalidValue;
-  auto block_rows = [](int64_t ld) -> int64_t {
-    const int64_t r = (kLim - 1) / ld;
-    return r >= 256 ? r / 256 * 256 : (r > 0 ? r : 1);
-  };
-  const int64_t cbytes = g.out == 1 ? 2 : 4;
-  if (g.m * g.lda >= kLim) {
-    const int64_t rows = block_rows(g.lda);
-    for (int64_t r = 0; r < g.m; r += rows) {
-      GemmParams sub = g;
-      sub.a = g.a + r * g.lda;
-      sub.m = g.m - r < rows ? g.m - r : rows;
-      sub.c = static_cast<char *>(g.c) + r * g.ldc * cbytes;
-      const hipError_t e = launch_gemm(sub, s, r + rows >= g.m ? fused : nullptr);  // the update rides on the last
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+hipError_t launch_gemm_large(int tile, const GemmParams &g, hipStream_t s, const UpdateParams &u) {
+  switch (tile) {
+    case kTile256x192: return launch_w4_fmts<256, 192>(g, s, u);
+    case kTile192x256: return launch_w4_fmts<192, 256>(g, s, u);
+    case kTile256x224: return launch_w4_fmts<256, 224>(g, s, u);
+    default: return launch_w4_fmts<256, 256>(g, s, u);
   }
-  if (g.n * g.ldb >= kLim) {
-    const int64_t cols = block_rows(g.ldb);
-    for (int64_t c0 = 0; c0 < g.n; c0 += cols) {
-      GemmParams sub = g;
-      sub.b = g.b + c0 * g.ldb;
-      sub.n = g.n - c0 < cols ? g.n - c0 : cols;
-      sub.c = static_cast<char *>(g.c) + c0 * cbytes;
-      const hipError_t e = launch_gemm(sub, s, c0 + cols >= g.n ? fused : nullptr);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  // Tile choice by wave quantization: each CU runs one workgroup at a time, so
-  // a grid costs ceil(tiles / CUs) rounds of one tile's time; the smaller tiles
-  // win where the 256 x 256 grid leaves its last round mostly empty (N = 6144:
-  // 384 tiles = 1.5 rounds, against 512 tiles of 256 x 192 = 2 rounds of 0.89;
-  // N = 14336: 896 tiles = 3.5 rounds, against 1024 of 256 x 224 = 4 of 0.98).
-  const int64_t cus = cu_count();
-  auto rounds = [&](int64_t bm, int64_t bn) {
-    const int64_t t = ((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn);
-    return double((t + cus - 1) / cus);
-  };
-  const int force = g_tile_override.load(std::memory_order_relaxed);
-  const double c256 = rounds(256, 256);
-  const double c128 = kCost128 * rounds(256, 128);
-  const double cn192 = kCost192 * rounds(256, 192);
-  const double cm192 = kCost192 * rounds(192, 256);
-  const double cn224 = kCost224 * rounds(256, 224);
-  // the 8-wave kernel has 512 lanes per workgroup: its update runs as a launch of its own
-  auto eight_wave = [&]() {
-    const hipError_t e = launch_fmts<256, 128, 4, 2>(g, s);
-    return e != hipSuccess || u.n == 0 ? e : launch_scale_update(u, s);
-  };
-  if (force == 1) return launch_w4_fmts<256, 256>(g, s, u);
-  if (force == 2) return launch_w4_fmts<256, 192>(g, s, u);
-  if (force == 3) return launch_w4_fmts<192, 256>(g, s, u);
-  if (force == 4) return eight_wave();
-  if (force == 5) return launch_w4_fmts<256, 224>(g, s, u);
-  double best = c256;
-  int pick = 1;
-  if (cn224 < best) { best = cn224; pick = 5; }
-  if (cn192 < best) { best = cn192; pick = 2; }
-  if (cm192 < best) { best = cm192; pick = 3; }
-  if (c128 < best) { best = c128; pick = 4; }
-  if (pick == 2) return launch_w4_fmts<256, 192>(g, s, u);
-  if (pick == 3) return launch_w4_fmts<192, 256>(g, s, u);
-  if (pick == 4) return eight_wave();
-  if (pick == 5) return launch_w4_fmts<256, 224>(g, s, u);
-  return launch_w4_fmts<256, 256>(g, s, u);
 }
-
-void set_gemm_tile_override(int tile) { g_tile_override.store(tile, std::memory_order_relaxed); }
 
 }  // namespace qe

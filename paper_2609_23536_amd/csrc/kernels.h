@@ -184,10 +184,31 @@ hipError_t launch_quantize(const QuantParams &p, hipStream_t s);
 hipError_t launch_quantize_pair(const QuantParams &a, const QuantParams &b, hipStream_t s);
 // `fused`, if non-null, is a delayed scale update (n >= 1 roles) run in extra
 // workgroups of the same launch (or in a launch of its own right after it when
-// the GEMM is empty or uses the 8-wave kernel); the GEMM must not read the
-// live scales it writes.
+// the GEMM is empty); the GEMM must not read the live scales it writes.
 hipError_t launch_gemm(const GemmParams &p, hipStream_t s, const UpdateParams *fused = nullptr);
-// 0: tile shape from the cost model; 1..4: force 256x256, 256x192, 192x256, 256x128
+// Tile shapes: the values of qe_gemm_tile (gemm_fp8.hip; 256 x 128, which the
+// cost model never picks, in gemm_ring.hip), then the small ones (gemm_ring.hip;
+// "Deep": twice the LDS stages, one workgroup per compute unit instead of two).
+enum GemmTile {
+  kTileAuto = 0,
+  kTile256x256 = 1,
+  kTile256x192 = 2,
+  kTile192x256 = 3,
+  kTile256x128 = 4,
+  kTile256x224 = 5,
+  kTile64x64 = 6,
+  kTile128x64 = 7,
+  kTile128x64Deep = 8,
+  kTile64x128 = 9,
+  kTile64x128Deep = 10,
+  kTile128x128 = 11,
+  kTile128x128Deep = 12,
+};
+// One launch of a product whose operands are below 2 GiB each; the update runs
+// as in launch_gemm.
+hipError_t launch_gemm_large(int tile, const GemmParams &g, hipStream_t s, const UpdateParams &u);
+hipError_t launch_gemm_ring(int tile, const GemmParams &g, hipStream_t s, const UpdateParams &u);
+// 0: tile shape from the cost model, else one shape for every product
 void set_gemm_tile_override(int tile);
 hipError_t launch_grad_copy(const GradCopyParams &p, hipStream_t s);
 hipError_t launch_amax(const AmaxParams &p, hipStream_t s);

@@ -242,6 +242,44 @@ def test_tile_shapes_same_bits(forced_tile, shape):
     for o in outs[1:]:
         np.testing.assert_array_equal(o, outs[0])
 
+# shapes the cost model gives to each small tile (64x64; 128x64 and 64x128 with
+# one and with several workgroups per compute unit; 128x128 likewise), with one
+# to nine K tiles, full and partial last ones, and edges of one row or column
+SMALL_TILE_SHAPES = [(1, 1, 1), (65, 63, 129), (64, 64, 512), (129, 200, 1152), (256, 256, 1029), (1000, 1365, 1000),
+                     (1365, 1000, 257), (2048, 1030, 768), (1030, 2048, 640), (512, 4096, 1500), (4096, 513, 1408),
+                     (2048, 2050, 1152), (1024, 4096, 1100), (2049, 4095, 384)]
+
+
+@pytest.mark.parametrize("shape", SMALL_TILE_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_small_tiles_same_bits_as_large(forced_tile, shape):
+    """The tile the cost model picks gives the bits of the 256 x 256 tile on
+    random codes, with codes of NaN past K in the operands' padding: FP32, BF16
+    and accumulate, on vector-aligned and odd row strides; columns past N stay
+    untouched."""
+    qe = forced_tile
+    d = dev()
+    m, n, k = shape
+    rng = np.random.default_rng(m + 3 * n + 7 * k)
+    A = random_codes(rng, m, k, 1, rup16(k))
+    B = random_codes(rng, n, k, 0, rup16(k))
+    A[:, k:], B[:, k:] = 0x7F, 0x7F
+    a_t, b_t = torch.from_numpy(A).to(d), torch.from_numpy(B).to(d)
+    s = torch.tensor([2.0 ** -2, 2.0 ** 3], dtype=torch.float32, device=d)
+    g = torch.Generator(device=d)
+    for out, mode in ((qe.F32, qe.INIT), (qe.BF16, qe.INIT), (qe.F32, qe.ACCUM)):
+        for ldc in (rup16(n), rup16(n) + 3):
+            c0 = torch.randn((m, ldc), generator=g.manual_seed(7), device=d)
+            c0 = c0.to(torch.bfloat16) if out == qe.BF16 else c0
+            got = []
+            for tile in (1, 0):
+                assert qe.qe_set_gemm_tile(tile) == "OK"
+                c = c0.clone()
+                assert qe.qe_fp8_gemm_tn(a_t, 1, A.shape[1], b_t, 0, B.shape[1], m, n, k, s[0:1], s[1:2], c, out, ldc,
+                                         mode) == "OK"
+                got.append(c.view(torch.int16 if out == qe.BF16 else torch.int32))
+            assert torch.equal(got[0], got[1])
+            assert torch.equal(got[1][:, n:], c0.view(got[1].dtype)[:, n:])
+
 
 def _lut_codes(d, seed, rows, cols, lo, hi, fmt):
     """Device operands of small integers lo..hi as FP8 codes (exact in either
