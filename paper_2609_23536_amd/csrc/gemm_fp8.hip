@@ -35,10 +35,10 @@
 // read), the A part in the first half of phase B; a second barrier per K step
 // marks the B half free.  (Measured on MI355X: against all loads spread over
 // phase B, the Llama-3-70B stage's GEMMs 4% faster, products whose operands
-// stream from HBM up to 8%.)  LDS rows are 128 bytes; their 16-byte chunks are
-// XOR-swizzled by (row/2) mod 8 so a fragment read hits the 64 banks evenly,
-// and since fragments start on multiples of 16 rows, every fragment of a wave
-// is one base address plus a constant.  The LDS-bound loads are inline
+// stream from HBM up to 8%.)  LDS rows are 128 bytes, their 16-byte chunks
+// XOR-swizzled by row (row_swizzle) so that a fragment read meets no bank
+// conflict, and since fragments start on multiples of 16 rows, every fragment
+// of a wave is one base address plus a constant.  The LDS-bound loads are inline
 // assembly: the compiler's own form makes it wait for them before every LDS
 // read, serialising the loads with the MFMA work.  Rows past M / N are
 // clamped to the last row (their results are never stored), so only the last,
@@ -136,13 +136,13 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
 #pragma unroll
   for (int c = 0; c < CHA; ++c) {
     const int row = 8 * (wave + NW * c) + lrow;
-    const int lch = (lane & 7) ^ ((row >> 1) & 7);
+    const int lch = (lane & 7) ^ row_swizzle(row);
     oa[c] = uint32_t(min(m0 + row, M - 1) * g.lda) + lch * 16;
   }
 #pragma unroll
   for (int c = 0; c < CHB; ++c) {
     const int row = 8 * (wave + NW * c) + lrow;
-    const int lch = (lane & 7) ^ ((row >> 1) & 7);
+    const int lch = (lane & 7) ^ row_swizzle(row);
     ob[c] = uint32_t(min(n0 + row, N - 1) * g.ldb) + lch * 16;
   }
   const uint32_t lds_base = uint32_t(reinterpret_cast<uintptr_t>(smem));
@@ -170,14 +170,14 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
 #pragma unroll
       for (int c = 0; c < CHA; ++c) {
         const int row = 8 * (wave + NW * c) + lrow;
-        const int64_t gk = int64_t(k0) + (((lane & 7) ^ ((row >> 1) & 7)) * 16);
+        const int64_t gk = int64_t(k0) + ((lane & 7) ^ row_swizzle(row)) * 16;
         const uint4 va = gk < K ? mask_tail(*reinterpret_cast<const uint4 *>(g.a + (oa[c] + k0)), K - gk) : make_uint4(0u, 0u, 0u, 0u);
         *reinterpret_cast<uint4 *>(dA + (wave + NW * c) * 1024 + lane * 16) = va;
       }
 #pragma unroll
       for (int c = 0; c < CHB; ++c) {
         const int row = 8 * (wave + NW * c) + lrow;
-        const int64_t gk = int64_t(k0) + (((lane & 7) ^ ((row >> 1) & 7)) * 16);
+        const int64_t gk = int64_t(k0) + ((lane & 7) ^ row_swizzle(row)) * 16;
         const uint4 vb = gk < K ? mask_tail(*reinterpret_cast<const uint4 *>(g.b + (ob[c] + k0)), K - gk) : make_uint4(0u, 0u, 0u, 0u);
         *reinterpret_cast<uint4 *>(dB + (wave + NW * c) * 1024 + lane * 16) = vb;
       }
@@ -188,8 +188,8 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
   // of the K tile, i.e. logical chunks 2 (l >> 4) and the next.  The swizzle
   // term depends on (l & 15) only, so every fragment is base + constant.
   const int fr = lane & 15, fq = lane >> 4;
-  const uint32_t f_lo = uint32_t(fr) * BK + (uint32_t((2 * fq) ^ (fr >> 1)) & 7) * 16;
-  const uint32_t f_hi = uint32_t(fr) * BK + (uint32_t((2 * fq + 1) ^ (fr >> 1)) & 7) * 16;
+  const uint32_t f_lo = uint32_t(fr) * BK + uint32_t((2 * fq) ^ row_swizzle(fr)) * 16;
+  const uint32_t f_hi = uint32_t(fr) * BK + uint32_t((2 * fq + 1) ^ row_swizzle(fr)) * 16;
   auto frag = [&](const uint8_t *base) -> v8i {
     const uint4 lo = *reinterpret_cast<const uint4 *>(base + f_lo);
     const uint4 hi = *reinterpret_cast<const uint4 *>(base + f_hi);
