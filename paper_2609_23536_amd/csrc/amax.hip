@@ -31,6 +31,8 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kUnroll = 16;            // 256 bytes per lane in flight per batch (cached loads)
+constexpr int kUnrollSmall = 4;        // 64 bytes: four times the workgroups
+constexpr int64_t kSmallVec = int64_t(1024) * kThreads * kUnrollSmall;  // up to here (16 MB, four workgroups per CU)
 constexpr int kUnrollNT = 4;           // 64 bytes (non-temporal loads)
 constexpr int64_t kNTBytes = int64_t(256) << 20;  // the memory-side cache of MI355X
 constexpr int64_t kMaxBlocks = 4096;     // cached loads: 16 workgroups per CU
@@ -47,26 +49,33 @@ __device__ __forceinline__ uint32_t word_abs(uint32_t w) {
   return w & 0x7fffffffu;
 }
 
-template <bool BF16, bool NT>
+template <bool BF16, int U, bool NT>
 __global__ __launch_bounds__(kThreads) void amax_kernel(AmaxParams p) {
-  constexpr int kU = NT ? kUnrollNT : kUnroll;
   const int tid = threadIdx.x;
   const u32x4 *v = reinterpret_cast<const u32x4 *>(static_cast<const char *>(p.in) + p.body_offset);
   const int64_t stride = int64_t(gridDim.x) * kThreads;
   int64_t i = int64_t(blockIdx.x) * kThreads + tid;
   uint32_t m = 0;
-  for (; i + (kU - 1) * stride < p.nvec; i += kU * stride) {
-    u32x4 r[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) r[u] = NT ? __builtin_nontemporal_load(v + i + u * stride) : v[i + u * stride];
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-      m = umax(m, umax(umax(word_abs<BF16>(r[u].x), word_abs<BF16>(r[u].y)),
-                       umax(word_abs<BF16>(r[u].z), word_abs<BF16>(r[u].w))));
-  }
-  for (; i < p.nvec; i += stride) {
-    const u32x4 r = NT ? __builtin_nontemporal_load(v + i) : v[i];
+  auto load = [&](int64_t at) -> u32x4 { return NT ? __builtin_nontemporal_load(v + at) : v[at]; };
+  auto fold = [&](const u32x4 &r) {
     m = umax(m, umax(umax(word_abs<BF16>(r.x), word_abs<BF16>(r.y)), umax(word_abs<BF16>(r.z), word_abs<BF16>(r.w))));
+  };
+  for (; i + (U - 1) * stride < p.nvec; i += U * stride) {
+    u32x4 r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = load(i + u * stride);
+#pragma unroll
+    for (int u = 0; u < U; ++u) fold(r[u]);
+  }
+  if (i < p.nvec) {  // the last, partial batch: its loads in flight together too
+    u32x4 r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      r[u] = u32x4{0u, 0u, 0u, 0u};
+      if (i + u * stride < p.nvec) r[u] = load(i + u * stride);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) fold(r[u]);
   }
   if (blockIdx.x == 0 && tid < p.head + p.tail) {
     const int64_t e = tid < p.head ? int64_t(tid) : p.tail_start + (tid - p.head);
@@ -85,13 +94,35 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(AmaxParams p) {
     uint32_t a = red[0];
 #pragma unroll
     for (int w = 1; w < kThreads / 64; ++w) a = umax(a, red[w]);
-    fold_amax(p.accum, p.amax, a);
+    if (p.partials != nullptr) {
+      if (blockIdx.x == 0) a = umax(a, __float_as_uint(*p.amax) & 0x7fffffffu);
+      p.partials[blockIdx.x] = __uint_as_float(a);
+    } else {
+      fold_amax(p.accum, p.amax, a);
+    }
   }
 }
 
 __global__ __launch_bounds__(kThreads) void fill_zero_kernel(float *p, int64_t n) {
   for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < n; i += int64_t(gridDim.x) * kThreads)
     p[i] = 0.0f;
+}
+
+struct AmaxShape {
+  bool nt;
+  int unroll;
+  int64_t blocks;
+};
+
+AmaxShape amax_shape(const AmaxParams &p) {
+  AmaxShape a;
+  a.nt = p.nvec * 16 > kNTBytes;
+  a.unroll = a.nt ? kUnrollNT : (p.nvec <= kSmallVec ? kUnrollSmall : kUnroll);
+  const int64_t per = int64_t(kThreads) * a.unroll;
+  a.blocks = (p.nvec + per - 1) / per;
+  if (a.blocks > (a.nt ? kMaxBlocksNT : kMaxBlocks)) a.blocks = a.nt ? kMaxBlocksNT : kMaxBlocks;
+  if (a.blocks < 1) a.blocks = 1;
+  return a;
 }
 
 }  // namespace
@@ -105,16 +136,19 @@ hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t s) {
 
 hipError_t launch_amax(const AmaxParams &p, hipStream_t s) {
   if (p.nvec == 0 && p.head + p.tail == 0) return hipSuccess;  // empty tensor: amax 0, nothing to fold
-  const bool nt = p.nvec * 16 > kNTBytes;
-  const int64_t per = int64_t(kThreads) * (nt ? kUnrollNT : kUnroll);
-  int64_t blocks = (p.nvec + per - 1) / per;
-  if (blocks > (nt ? kMaxBlocksNT : kMaxBlocks)) blocks = nt ? kMaxBlocksNT : kMaxBlocks;
-  if (blocks < 1) blocks = 1;
-  const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-  if (nt)
-    return p.in_bf16 ? klaunch(amax_kernel<true, true>, grid, block, 0, s, p) : klaunch(amax_kernel<false, true>, grid, block, 0, s, p);
-  return p.in_bf16 ? klaunch(amax_kernel<true, false>, grid, block, 0, s, p) : klaunch(amax_kernel<false, false>, grid, block, 0, s, p);
+  const AmaxShape a = amax_shape(p);
+  const dim3 grid(static_cast<unsigned>(a.blocks)), block(kThreads);
+  if (a.nt)
+    return p.in_bf16 ? klaunch(amax_kernel<true, kUnrollNT, true>, grid, block, 0, s, p)
+                     : klaunch(amax_kernel<false, kUnrollNT, true>, grid, block, 0, s, p);
+  if (a.unroll == kUnrollSmall)
+    return p.in_bf16 ? klaunch(amax_kernel<true, kUnrollSmall, false>, grid, block, 0, s, p)
+                     : klaunch(amax_kernel<false, kUnrollSmall, false>, grid, block, 0, s, p);
+  return p.in_bf16 ? klaunch(amax_kernel<true, kUnroll, false>, grid, block, 0, s, p)
+                   : klaunch(amax_kernel<false, kUnroll, false>, grid, block, 0, s, p);
 }
+
+int amax_blocks(const AmaxParams &p) { return int(amax_shape(p).blocks); }
 
 AmaxParams amax_params(const void *in, bool bf16, int64_t numel, float *amax, float *accum) {
   AmaxParams p;

@@ -833,6 +833,12 @@ qe_status qe_quantize_fp8_current_noalloc(const void *in, qe_dtype in_dtype, int
   u.n = 1;
   u.token = reinterpret_cast<long long *>(device_token);
   const Call q = quant_call(in, in_dtype, rows, cols, m, q_row, ld_row, q_col, ld_col, scale_inv_snapshot, false);
+  // Up to 64 MB (kMaxPartials workgroups of the amax pass) the cast derives the
+  // scale itself from partial maxima in the scratch: two launches.  Beyond,
+  // re-reading them in every workgroup and an amax pass of few workgroups cost
+  // more than the two launches saved.
+  if (rows > 0 && cols > 0 && qe::amax_blocks(a.a) <= qe::kMaxPartials)
+    return qe::launch_quantize_current(a.a, q.q, m, u.token, acc, s) == hipSuccess ? QE_OK : QE_ERR_HIP;
   // the scratch keeps the last call's contents: cleared first, by a kernel
   if (qe::launch_fill_zero(acc, int64_t(qe::kAmaxLines) * qe::kAmaxStride, s) != hipSuccess ||
       qe::launch_amax(a.a, s) != hipSuccess || qe::launch_scale_update(u, s) != hipSuccess ||

@@ -170,10 +170,24 @@ struct AmaxParams {
   const void *in;
   float *amax;   // single float slot (used when accum is null)
   float *accum;  // amax accumulator
+  // if set, workgroup w writes its max to partials[w] instead (workgroup 0's
+  // includes *amax): nothing to clear beforehand, and no atomics
+  float *partials;
   int64_t body_offset, nvec, tail_start;
   int32_t head, tail;
   int32_t in_bf16;
   int32_t pad;
+};
+
+// The scale update of a current-scaling role, done by the cast itself from the
+// amax pass's partial maxima.
+constexpr int kMaxPartials = 1024;
+struct CurrentParams {
+  MetaRef m;  // history_len 1
+  const float *partials;
+  int32_t n;
+  int32_t pad;
+  long long *token;  // incremented when non-null
 };
 
 enum KernelClass { KC_QUANT = 0, KC_UPDATE = 1, KC_GEMM = 2, KC_COPY = 3, KC_AMAX = 4, KC_COUNT = 5 };
@@ -182,6 +196,12 @@ hipError_t launch_scale_update(const UpdateParams &p, hipStream_t s);
 hipError_t launch_quantize(const QuantParams &p, hipStream_t s);
 // Two independent casts with the same input dtype and FP8 format in one launch.
 hipError_t launch_quantize_pair(const QuantParams &a, const QuantParams &b, hipStream_t s);
+// Current-scaling cast in two launches: the amax pass (partial maxima into
+// `partials`, kMaxPartials floats), then the cast, every workgroup of which
+// derives the scale from them.  hipErrorInvalidValue, with nothing launched,
+// for a tensor it does not serve (empty, or its pass has more than kMaxPartials workgroups).
+hipError_t launch_quantize_current(const AmaxParams &a, const QuantParams &q, const MetaRef &m, long long *token,
+                                   float *partials, hipStream_t s);
 // `fused`, if non-null, is a delayed scale update (n >= 1 roles) run in extra
 // workgroups of the same launch (or in a launch of its own right after it when
 // the GEMM is empty); the GEMM must not read the live scales it writes.
@@ -212,6 +232,7 @@ hipError_t launch_gemm_ring(int tile, const GemmParams &g, hipStream_t s, const 
 void set_gemm_tile_override(int tile);
 hipError_t launch_grad_copy(const GradCopyParams &p, hipStream_t s);
 hipError_t launch_amax(const AmaxParams &p, hipStream_t s);
+int amax_blocks(const AmaxParams &p);  // the workgroups launch_amax starts
 // p[0..n) = 0 with a kernel (no memset node when captured into a graph)
 hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t s);
 AmaxParams amax_params(const void *in, bool bf16, int64_t numel, float *amax, float *accum);

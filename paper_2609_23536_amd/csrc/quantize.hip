@@ -21,7 +21,17 @@
 // reduction, then one atomicMax per workgroup into one of the 64 lines of the
 // role's amax accumulator (same-line atomics serialise).  HBM-bound: per element it
 // moves 2 or 4 bytes in and 2 bytes out.
-#include "kernels.h"
+//
+// Rows need no alignment beyond the element's: the global accesses are the same
+// single 16-, 8- and 4-byte instructions at any address (unaligned access is
+// the normal mode of the device), and a tile at the tensor's edge guards each
+// of them instead of falling back to single elements.  Measured on MI355X, one
+// step of a 1365 x 2730 layer with two 1000-token microbatches (no row 16-byte
+// aligned): 236 us with single elements, 151 us so; 1500 x 4099 fp32 current
+// cast, with the scale derived in the cast (CurrentParams): 46 -> 19 us.
+#include "scale_update.h"
+
+#include <type_traits>
 
 namespace qe {
 namespace {
@@ -29,7 +39,11 @@ namespace {
 constexpr int kTile = 128;
 constexpr int kThreads = 256;
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// Vectors at element (input) and byte (code) alignment.
+typedef unsigned int u32x4_in __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned int u32x4_out __attribute__((ext_vector_type(4), aligned(1)));
+typedef unsigned int u32x2_out __attribute__((ext_vector_type(2), aligned(1)));
+typedef unsigned int u32_out __attribute__((aligned(1)));
 
 // Four scaled values -> four FP8 codes, byte i = value i.  The hardware
 // conversion rounds to nearest even but neither saturates (it overflows to
@@ -95,15 +109,15 @@ __device__ __forceinline__ void unpack16(const uint4 &v, float *f) {
 struct QuantJob {
   QuantParams p;
   int64_t tiles, tiles_c;
-  int32_t aligned, pad;
 };
 struct QuantPair {
   QuantJob j[2];
   int32_t n, pad;
 };
 
-template <bool BF16, int FMT>
-__global__ __launch_bounds__(kThreads) void quantize_kernel(QuantPair pp) {
+// CUR: the cast of a current-scaling role derives its own scale (see scale_of).
+template <bool BF16, int FMT, bool CUR>
+__device__ __forceinline__ void quantize_body(const QuantPair &pp, const CurrentParams &cp) {
   __shared__ __attribute__((aligned(16))) uint8_t tile[kTile * kTile];
   __shared__ uint32_t red[kThreads / 64];
   // Phase 1 mapping: one 16-byte load per lane per step, consecutive lanes on
@@ -116,110 +130,171 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantPair pp) {
   const QuantJob &job = second ? pp.j[1] : pp.j[0];
   const QuantParams &p = job.p;
   const int64_t tiles_c = job.tiles_c;
-  const int aligned = job.aligned;
   const int64_t t = second ? int64_t(blockIdx.x) - pp.j[0].tiles : int64_t(blockIdx.x);
   const int64_t r0 = (t / tiles_c) * kTile;
   const int64_t c0 = (t % tiles_c) * kTile;
-  const float scale = *p.scale;
-  if (t == 0 && tid == 0 && p.snapshot != nullptr) *p.snapshot = *p.scale_inv;
-  const bool full = aligned && r0 + kTile <= p.rows && c0 + kTile <= p.cols;
+  // The scale.  Under CUR every workgroup reduces the amax pass's partial
+  // maxima (at most kMaxPartials floats, from the L2) instead of waiting for
+  // an update kernel; the first one stores the role's new state, which the
+  // others never read: they read the live scale only where the amax leaves it
+  // as it is.
+  auto scale_of = [&]() -> float {
+    if constexpr (!CUR) {
+      if (t == 0 && tid == 0 && p.snapshot != nullptr) *p.snapshot = *p.scale_inv;
+      return *p.scale;
+    } else {
+      uint32_t a = 0;
+#pragma unroll
+      for (int k = 0; k < kMaxPartials / kThreads; ++k)
+        if (k * kThreads + tid < cp.n) {
+          const uint32_t b = __float_as_uint(cp.partials[k * kThreads + tid]);
+          a = b > a ? b : a;
+        }
+      a = update_wave_max(a);
+      if ((tid & 63) == 0) red[tid >> 6] = a;
+      __syncthreads();
+      a = red[0];
+#pragma unroll
+      for (int w = 1; w < kThreads / 64; ++w) a = red[w] > a ? red[w] : a;
+      int e;
+      const bool valid = update_exponent(a, cp.m.fmt, cp.m.margin, &e);
+      const float sc = valid ? __uint_as_float(uint32_t(e + 127) << 23) : *p.scale;
+      if (t == 0 && tid == 0) {
+        const float inv = valid ? __uint_as_float(uint32_t(127 - e) << 23) : *p.scale_inv;
+        if (valid) {
+          *cp.m.scale = sc;
+          *cp.m.scale_inv = inv;
+        }
+        cp.m.hist[0] = 0.0f;
+        if (p.snapshot != nullptr) *p.snapshot = inv;
+        if (cp.token != nullptr) __hip_atomic_fetch_add(cp.token, 1ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      return sc;
+    }
+  };
+  const float scale = scale_of();
+  const bool full = r0 + kTile <= p.rows && c0 + kTile <= p.cols;
   uint32_t amax = 0;
 
-  if (full) {
-    uint4 raw[NLD];
+  // Phase 1, for whole tiles (EDGE false) and tiles at the tensor's edge: a
+  // lane's elements past the last column or row count as zero and are not
+  // stored.  Edge tiles take their steps in two groups, so that their guards
+  // cost the whole tiles no registers.
+  auto cast_tile = [&](auto edge) {
+    constexpr bool EDGE = decltype(edge)::value;
+    // valid elements of the lane's piece of step `it`
+    auto valid = [&](int it) -> int {
+      const int q = it * kThreads + tid;
+      const int64_t left = r0 + q / LPR < p.rows ? p.cols - (c0 + q % LPR * EPL) : 0;
+      return left <= 0 ? 0 : (left >= EPL ? EPL : int(left));
+    };
+    constexpr int G = EDGE ? NLD / 2 : NLD;
+#pragma unroll 1
+    for (int g = 0; g < NLD; g += G) {
+      uint4 raw[G];
 #pragma unroll
-    for (int it = 0; it < NLD; ++it) {
-      const int q = it * kThreads + tid, row = q / LPR, cl = q % LPR;
-      const int64_t eoff = (r0 + row) * p.cols + c0 + cl * EPL;
-      const u32x4 x = __builtin_nontemporal_load(
-          reinterpret_cast<const u32x4 *>(static_cast<const char *>(p.in) + eoff * (BF16 ? 2 : 4)));
-      raw[it] = make_uint4(x.x, x.y, x.z, x.w);
-    }
-    uint32_t codes[NLD][EPL / 4];
+      for (int u = 0; u < G; ++u) {
+        const int q = (g + u) * kThreads + tid, row = q / LPR, cl = q % LPR;
+        const int64_t eoff = (r0 + row) * p.cols + c0 + cl * EPL;
+        const char *src = static_cast<const char *>(p.in) + eoff * (BF16 ? 2 : 4);
+        if constexpr (!EDGE) {
+          const u32x4_in x = __builtin_nontemporal_load(reinterpret_cast<const u32x4_in *>(src));
+          raw[u] = make_uint4(x.x, x.y, x.z, x.w);
+        } else {
+          const int n = valid(g + u);
+          raw[u] = make_uint4(0u, 0u, 0u, 0u);
+          if (n > 0) {
+            if (eoff + EPL <= p.rows * p.cols) {  // may run into the next row; masked below
+              const u32x4_in x = *reinterpret_cast<const u32x4_in *>(src);
+              raw[u] = make_uint4(x.x, x.y, x.z, x.w);
+            } else {  // the tensor's last elements
+              uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int it = 0; it < NLD; ++it) {
-      float f[EPL];
-      unpack16<BF16>(raw[it], f);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const uint32_t b = abs_bits(f[e]);
-        amax = b > amax ? b : amax;
+              for (int e = 0; e < EPL; ++e) {
+                if (e >= n) break;
+                if constexpr (BF16)
+                  w[e / 2] |= uint32_t(reinterpret_cast<const uint16_t *>(src)[e]) << (16 * (e % 2));
+                else
+                  w[e] = reinterpret_cast<const uint32_t *>(src)[e];
+              }
+              raw[u] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+          }
+        }
       }
+      auto values = [&](int u, float *f) {
+        unpack16<BF16>(raw[u], f);
+        if constexpr (EDGE) {
+          const int n = valid(g + u);
 #pragma unroll
-      for (int w = 0; w < EPL / 4; ++w)
-        codes[it][w] = enc4<FMT>(f[4 * w] * scale, f[4 * w + 1] * scale, f[4 * w + 2] * scale, f[4 * w + 3] * scale);
-    }
-    if (__builtin_expect(amax > 0x7f800000u, 0)) {  // this lane saw a NaN
+          for (int e = 0; e < EPL; ++e) f[e] = e < n ? f[e] : 0.0f;
+        }
+      };
+      uint32_t codes[G][EPL / 4];
 #pragma unroll
-      for (int it = 0; it < NLD; ++it) {
+      for (int u = 0; u < G; ++u) {
         float f[EPL];
-        unpack16<BF16>(raw[it], f);
+        values(u, f);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) codes[it][e / 4] = nan_fix(codes[it][e / 4], e % 4, f[e]);
+        for (int e = 0; e < EPL; ++e) {
+          const uint32_t b = abs_bits(f[e]);
+          amax = b > amax ? b : amax;
+        }
+#pragma unroll
+        for (int w = 0; w < EPL / 4; ++w)
+          codes[u][w] = enc4<FMT>(f[4 * w] * scale, f[4 * w + 1] * scale, f[4 * w + 2] * scale, f[4 * w + 3] * scale);
       }
-    }
+      if (__builtin_expect(amax > 0x7f800000u, 0)) {  // this lane saw a NaN
 #pragma unroll
-    for (int it = 0; it < NLD; ++it) {
-      const int q = it * kThreads + tid, row = q / LPR, cl = q % LPR;
-      const int col = cl * EPL;
-      const uint32_t lofs = lds_chunk_offset(row, col >> 4) + (col & 15);
-      if constexpr (BF16) {
-        if (p.q_row != nullptr)
-          *reinterpret_cast<uint2 *>(p.q_row + (r0 + row) * p.ld_row + c0 + col) = make_uint2(codes[it][0], codes[it][1]);
-        *reinterpret_cast<uint2 *>(tile + lofs) = make_uint2(codes[it][0], codes[it][1]);
-      } else {
-        if (p.q_row != nullptr) *reinterpret_cast<uint32_t *>(p.q_row + (r0 + row) * p.ld_row + c0 + col) = codes[it][0];
-        *reinterpret_cast<uint32_t *>(tile + lofs) = codes[it][0];
+        for (int u = 0; u < G; ++u) {
+          float f[EPL];
+          values(u, f);
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) codes[u][e / 4] = nan_fix(codes[u][e / 4], e % 4, f[e]);
+        }
       }
-    }
-  } else {
-    for (int it = 0; it < 4; ++it) {
-      const int q = it * kThreads + tid, row = q >> 3, cc = q & 7;
-      const int64_t r = r0 + row;
-      float f[16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t c = c0 + cc * 16 + e;
-        float v = 0.0f;
-        if (r < p.rows && c < p.cols) {
+      for (int u = 0; u < G; ++u) {
+        const int q = (g + u) * kThreads + tid, row = q / LPR, cl = q % LPR;
+        const int col = cl * EPL;
+        uint8_t *lds = tile + lds_chunk_offset(row, col >> 4) + (col & 15);
+        if constexpr (BF16)
+          *reinterpret_cast<uint2 *>(lds) = make_uint2(codes[u][0], codes[u][1]);
+        else
+          *reinterpret_cast<uint32_t *>(lds) = codes[u][0];
+        if (p.q_row == nullptr) continue;
+        uint8_t *dst = p.q_row + (r0 + row) * p.ld_row + c0 + col;
+        const int n = EDGE ? valid(g + u) : EPL;
+        if (!EDGE || n == EPL) {
           if constexpr (BF16)
-            v = bf16_to_f32(static_cast<const uint16_t *>(p.in)[r * p.cols + c]);
+            *reinterpret_cast<u32x2_out *>(dst) = u32x2_out{codes[u][0], codes[u][1]};
           else
-            v = static_cast<const float *>(p.in)[r * p.cols + c];
-        }
-        f[e] = v;
-        const uint32_t b = abs_bits(v);
-        amax = b > amax ? b : amax;
-      }
-      uint32_t w[4];
+            *reinterpret_cast<u32_out *>(dst) = codes[u][0];
+        } else {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        w[k] = enc4<FMT>(f[4 * k] * scale, f[4 * k + 1] * scale, f[4 * k + 2] * scale, f[4 * k + 3] * scale);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[k] = nan_fix(w[k], e, f[4 * k + e]);
-      }
-      if (p.q_row != nullptr && r < p.rows) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int64_t c = c0 + cc * 16 + e;
-          if (c < p.cols) p.q_row[r * p.ld_row + c] = uint8_t(byte_of(w[e >> 2], e & 3));
+          for (int e = 0; e < EPL; ++e)
+            if (e < n) dst[e] = uint8_t(byte_of(codes[u][e / 4], e % 4));
         }
       }
-      *reinterpret_cast<uint4 *>(tile + lds_chunk_offset(row, cc)) = make_uint4(w[0], w[1], w[2], w[3]);
     }
-  }
+  };
+  if (full)
+    cast_tile(std::false_type{});
+  else
+    cast_tile(std::true_type{});
 
   // amax: wave shuffle reduction, then one atomic per workgroup
-  for (int off = 32; off > 0; off >>= 1) {
-    uint32_t o = __shfl_xor(amax, off, 64);
-    amax = o > amax ? o : amax;
-  }
-  if ((tid & 63) == 0) red[tid >> 6] = amax;
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t a = red[0];
-    for (int w = 1; w < kThreads / 64; ++w) a = red[w] > a ? red[w] : a;
-    fold_amax(p.amax_accum, p.amax_slot, a);
+  if constexpr (CUR) {
+    __syncthreads();
+  } else {
+    amax = update_wave_max(amax);
+    if ((tid & 63) == 0) red[tid >> 6] = amax;
+    __syncthreads();
+    if (tid == 0) {
+      uint32_t a = red[0];
+      for (int w = 1; w < kThreads / 64; ++w) a = red[w] > a ? red[w] : a;
+      fold_amax(p.amax_accum, p.amax_slot, a);
+    }
   }
 
   if (p.q_col == nullptr) return;
@@ -240,14 +315,38 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantPair pp) {
              (byte_of(d[4 * q + 3], j) << 24);
     const int64_t col = c0 + 4 * cq + j;
     const int64_t rbase = r0 + rb * 16;
+    uint8_t *dst = p.q_col + col * p.ld_col + rbase;
     if (full) {
-      *reinterpret_cast<uint4 *>(p.q_col + col * p.ld_col + rbase) = make_uint4(w[0], w[1], w[2], w[3]);
-    } else if (col < p.cols) {
+      *reinterpret_cast<u32x4_out *>(dst) = u32x4_out{w[0], w[1], w[2], w[3]};
+      continue;
+    }
+    if (col >= p.cols) continue;
+    if (rbase + 16 <= p.rows) {
+      *reinterpret_cast<u32x4_out *>(dst) = u32x4_out{w[0], w[1], w[2], w[3]};
+    } else {  // the last rows: whole words, then bytes
+      const int n = int(p.rows - rbase);
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (rbase + e < p.rows) p.q_col[col * p.ld_col + rbase + e] = uint8_t(byte_of(w[e >> 2], e & 3));
+      for (int q = 0; q < 4; ++q) {
+        if (4 * q + 4 <= n) {
+          *reinterpret_cast<u32_out *>(dst + 4 * q) = w[q];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (4 * q + e < n) dst[4 * q + e] = uint8_t(byte_of(w[q], e));
+        }
+      }
     }
   }
+}
+
+template <bool BF16, int FMT>
+__global__ __launch_bounds__(kThreads) void quantize_kernel(QuantPair pp) {
+  quantize_body<BF16, FMT, false>(pp, CurrentParams{});
+}
+
+template <bool BF16, int FMT>
+__global__ __launch_bounds__(kThreads) void quantize_current_kernel(QuantPair pp, CurrentParams cp) {
+  quantize_body<BF16, FMT, true>(pp, cp);
 }
 
 template <bool BF16>
@@ -267,11 +366,6 @@ QuantJob make_job(const QuantParams &p) {
   j.tiles = tiles_r * tiles_c;
   if (j.tiles < 1) j.tiles = 1;  // still writes the scale_inv snapshot
   j.tiles_c = tiles_c < 1 ? 1 : tiles_c;
-  const int64_t esize = p.in_bf16 ? 2 : 4;
-  const bool in_al = (reinterpret_cast<uintptr_t>(p.in) % 16 == 0) && ((p.cols * esize) % 16 == 0);
-  const bool row_al = p.q_row == nullptr || ((reinterpret_cast<uintptr_t>(p.q_row) % 16 == 0) && p.ld_row % 16 == 0);
-  const bool col_al = p.q_col == nullptr || ((reinterpret_cast<uintptr_t>(p.q_col) % 16 == 0) && p.ld_col % 16 == 0);
-  j.aligned = (in_al && row_al && col_al) ? 1 : 0;
   return j;
 }
 
@@ -287,6 +381,31 @@ hipError_t launch_quantize(const QuantParams &p, hipStream_t s) {
   pp.j[0] = make_job(p);
   pp.n = 1;
   return launch_pair(pp, s);
+}
+
+hipError_t launch_quantize_current(const AmaxParams &a, const QuantParams &q, const MetaRef &m, long long *token,
+                                   float *partials, hipStream_t s) {
+  if (q.rows * q.cols == 0 || amax_blocks(a) > kMaxPartials) return hipErrorInvalidValue;
+  AmaxParams ap = a;
+  ap.partials = partials;
+  CurrentParams cp;
+  memset(&cp, 0, sizeof(cp));
+  cp.m = m;
+  cp.partials = partials;
+  cp.n = amax_blocks(ap);
+  cp.token = token;
+  QuantPair pp;
+  memset(&pp, 0, sizeof(pp));
+  pp.j[0] = make_job(q);
+  pp.n = 1;
+  const hipError_t e = launch_amax(ap, s);
+  if (e != hipSuccess) return e;
+  const dim3 grid{unsigned(pp.j[0].tiles)}, block(kThreads);
+  if (q.in_bf16)
+    return q.fmt == 0 ? klaunch(quantize_current_kernel<true, 0>, grid, block, 0, s, pp, cp)
+                      : klaunch(quantize_current_kernel<true, 1>, grid, block, 0, s, pp, cp);
+  return q.fmt == 0 ? klaunch(quantize_current_kernel<false, 0>, grid, block, 0, s, pp, cp)
+                    : klaunch(quantize_current_kernel<false, 1>, grid, block, 0, s, pp, cp);
 }
 
 hipError_t launch_quantize_pair(const QuantParams &a, const QuantParams &b, hipStream_t s) {

@@ -29,6 +29,26 @@ __device__ __forceinline__ uint32_t update_wave_max(uint32_t v) {
   return v;
 }
 
+// The exponent of the scale for an amax (bit pattern a); false if a leaves the
+// scale as it is (zero, inf, NaN).
+__device__ __forceinline__ bool update_exponent(uint32_t a, int fmt, int margin, int *out) {
+  if (a == 0u || a >= 0x7f800000u) return false;
+  int E;
+  bool above;  // mantissa m > 1.75
+  if (a >= 0x00800000u) {
+    E = int(a >> 23) - 127;
+    above = (a & 0x007fffffu) > 0x00600000u;
+  } else {  // subnormal: a = f * 2^-149
+    const int pbit = 31 - __clz(a);
+    E = pbit - 149;
+    above = (uint64_t(a) << 2) > (uint64_t(7) << pbit);
+  }
+  const int emax = fmt == 0 ? 8 : 15;
+  const int e = emax - E - (above ? 1 : 0) - margin;
+  *out = e < -126 ? -126 : (e > 126 ? 126 : e);
+  return true;
+}
+
 // One workgroup of kUpdateThreads lanes updates role m.  hist_sh: LDS for
 // history_len words; red: LDS for kUpdateThreads / 64 words.  `token`, if
 // non-null, is incremented by this workgroup (pass it to one workgroup only).
@@ -75,20 +95,8 @@ __device__ __forceinline__ void scale_update_role(const MetaRef &m, long long *t
   if (tid == 0) {
     uint32_t a = red[0];
     for (int w = 1; w < kUpdateThreads / 64; ++w) a = red[w] > a ? red[w] : a;
-    if (a != 0u && a < 0x7f800000u) {
-      int E;
-      bool above;  // mantissa m > 1.75
-      if (a >= 0x00800000u) {
-        E = int(a >> 23) - 127;
-        above = (a & 0x007fffffu) > 0x00600000u;
-      } else {  // subnormal: a = f * 2^-149
-        int pbit = 31 - __clz(a);
-        E = pbit - 149;
-        above = (uint64_t(a) << 2) > (uint64_t(7) << pbit);
-      }
-      const int emax = m.fmt == 0 ? 8 : 15;
-      int e = emax - E - (above ? 1 : 0) - m.margin;
-      e = e < -126 ? -126 : (e > 126 ? 126 : e);
+    int e;
+    if (update_exponent(a, m.fmt, m.margin, &e)) {
       *m.scale = __uint_as_float(uint32_t(e + 127) << 23);
       *m.scale_inv = __uint_as_float(uint32_t(127 - e) << 23);
     }

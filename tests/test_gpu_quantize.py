@@ -119,6 +119,39 @@ def test_padded_leading_dimensions_untouched():
     assert (qr[:, cols:] == 0xA5).all() and (qc[:, rows:] == 0x5A).all()
 
 
+@pytest.mark.parametrize("shape", [(1, 3), (3, 1), (16, 7), (17, 8), (127, 129), (128, 131), (129, 128), (143, 255),
+                                   (252, 261), (272, 264)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_edge_tiles_unaligned(shape, dtype, shift):
+    """Edges of tiles and of 16-byte pieces in both directions, with the input one element and the outputs
+    one byte off every larger alignment; NaNs sit in the last row and column, and nothing outside the
+    codes is written."""
+    qe = need_lib()
+    d = dev()
+    rows, cols = shape
+    x = W.normal(W.rng_for(6, rows, cols, 0), shape, 3.0, dtype)
+    for r, c in ((rows - 1, cols - 1), (rows - 1, 0), (0, cols - 1)):
+        x.data[r, c] = np.nan if dtype == "f32" else 0xFFC1
+    t = upload(x, d)
+    buf = torch.full((rows * cols + shift,), 3, dtype=t.dtype, device=d)
+    buf[shift:].copy_(t.reshape(-1))
+    ldr, ldc = cols + 5 * shift, rows + 3 * shift
+    q_row = torch.full((shift + rows * ldr + 32,), 0xA5, dtype=torch.uint8, device=d)
+    q_col = torch.full((shift + cols * ldc + 32,), 0x5A, dtype=torch.uint8, device=d)
+    mb = meta_buffer(4, d, 8.0)
+    assert qe.qe_quantize_fp8(buf.data_ptr() + shift * buf.element_size(), qe.BF16 if dtype == "bf16" else qe.F32,
+                              rows, cols, meta_of(qe, mb, qe.E4M3), q_row.data_ptr() + shift, ldr,
+                              q_col.data_ptr() + shift, ldc) == "OK"
+    torch.cuda.synchronize()
+    want = gemm.quantize(x.as_f32(), 8.0, "E4M3")
+    for q, fill, ld, w in ((q_row, 0xA5, ldr, want), (q_col, 0x5A, ldc, want.T)):
+        full = np.full(q.numel(), fill, dtype=np.uint8)
+        full[shift:shift + w.shape[0] * ld].reshape(w.shape[0], ld)[:, :w.shape[1]] = w
+        np.testing.assert_array_equal(q.cpu().numpy(), full)
+    assert math.isnan(mb[0].item())
+
+
 def test_amax_accumulates_and_nan_propagates():
     qe = need_lib()
     d = dev()

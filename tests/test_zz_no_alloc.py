@@ -62,6 +62,34 @@ def test_noalloc_equals_current_cast_two_calls(fmt_name):
     assert not bool(torch.any(acc != 0))            # the caller's accumulator was cleared by its update
 
 
+def test_noalloc_either_side_of_the_two_launch_limit():
+    """4096 x 4096 fp32 is the largest tensor whose cast derives the scale from the amax pass's 1024 partial
+    maxima; 4097 x 4096 takes the accumulator.  The second's amax is the smaller one, so a maximum left
+    in the shared scratch would show, and an empty tensor between them keeps the scale."""
+    qe = need_lib()
+    d = dev()
+    ref_meta, new_meta = meta_buffer(1, d), meta_buffer(1, d)
+    ref_tok = torch.zeros(1, dtype=torch.int64, device=d)
+    new_tok = torch.zeros(1, dtype=torch.int64, device=d)
+    acc = accum_buffer(d)
+    g = torch.Generator(device=d)
+    g.manual_seed(9)
+    for rows, sigma in ((4096, 3.0), (0, 1.0), (4097, 0.01), (4096, 0.2)):
+        x = torch.randn((rows, 4096), generator=g, device=d) * sigma
+        out = []
+        for fn, meta, accum, tok in ((qe.qe_quantize_fp8_current, ref_meta, acc, ref_tok),
+                                     (qe.qe_quantize_fp8_current_noalloc, new_meta, None, new_tok)):
+            q_row, q_col = u8(rows * 4096, d), u8(4096 * rows, d)
+            snap = torch.zeros(1, dtype=torch.float32, device=d)
+            assert fn(x, qe.F32, rows, 4096, meta_of(qe, meta, qe.E4M3, accum=accum), q_row, 4096, q_col, rows,
+                      snap, tok) == "OK"
+            out.append((q_row, q_col, snap))
+        for a, b in zip(*out):
+            assert torch.equal(a, b)
+        assert torch.equal(ref_meta.view(torch.int32), new_meta.view(torch.int32))
+        assert ref_tok.item() == new_tok.item()
+
+
 def test_noalloc_rejects_a_caller_accumulator():
     qe = need_lib()
     d = dev()
