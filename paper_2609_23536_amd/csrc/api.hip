@@ -49,6 +49,17 @@ namespace {
 
 int64_t rup16(int64_t v) { return (v + 15) / 16 * 16; }
 
+// Row stride of the library's own code buffers, for rows of v codes: whole
+// 128-byte lines.  The GEMM loads 128-byte row pieces, and rows that start
+// inside a line make each piece two lines.  Measured on MI355X, 8192^3 with
+// strides of 8192 + 0 / 16 / 64 / 128: 395 / 472 / 435 / 379 us; 512 x 4096 x
+// 14336: 36.6 / 59.2 / 44.9 / 35.9; one step of a 1365 x 2730 layer with two
+// 1000-token microbatches 151 us with strides rounded to 16, 141 so.  (An odd
+// number of lines for long rows, 128 bytes more, gains on repeated products of
+// the same operands and nothing over a step: 818 and 2400 us against 818 and
+// 2409.)
+int64_t code_ld(int64_t v) { return (v + 127) / 128 * 128; }
+
 // Device address of `scratch` on the current device, looked up once per
 // device (each device holds its own copy at its own address).
 constexpr int kScratchDevices = 64;
@@ -958,11 +969,11 @@ qe_status qe_layer_register(qe_ctx *c, const qe_layer_desc *d, int32_t *layer_ou
   L.desc = *d;
   const int M = c->cfg.microbatches;
   L.slots.resize(size_t(M));
-  L.ld_wq = rup16(d->k_in);
-  L.ld_wqt = rup16(d->n_out);
-  L.ld_xq = rup16(d->k_in);
-  L.ld_dyq = rup16(d->n_out);
-  L.ld_t = rup16(d->max_tokens);
+  L.ld_wq = code_ld(d->k_in);
+  L.ld_wqt = code_ld(d->n_out);
+  L.ld_xq = code_ld(d->k_in);
+  L.ld_dyq = code_ld(d->n_out);
+  L.ld_t = code_ld(d->max_tokens);
   if (!c->cfg.null_executor) {
     DeviceGuard dg(c->cfg.device);
     if (!dg.ok) return QE_ERR_HIP;
