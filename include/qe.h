@@ -237,7 +237,10 @@ typedef struct qe_ctx qe_ctx;
 typedef struct {
   int32_t device;        /* HIP device ordinal */
   int32_t microbatches;  /* M: tape slots per layer, slot p = microbatch m */
-  int32_t use_graphs;    /* 1: capture each (layer, action, slot) sequence once and replay it */
+  int32_t use_graphs;    /* 1: capture each (layer, action, slot) sequence once and replay it.  A captured
+                            chain of up to eight kernels (every action but those on products split at
+                            2 GiB) is replayed by enqueuing its launches on the stream, a longer one
+                            by hipGraphLaunch; order and results are the same. */
   int32_t null_executor; /* 1: run the contract only, no HIP call at all (host-only testing) */
   int32_t one_way_handoff; /* testing only: skip the caller's wait on the graph tail (§2.3) */
   int32_t copy_gradients;  /* 1: dW goes to a private FP32 buffer, then is copied into the bound view
@@ -256,9 +259,9 @@ typedef struct {
   int32_t graph_inputs;     /* how a replayed graph meets the buffers of each call (§4.4, dynamic
                               inputs); use_graphs only.  QE_GRAPH_INPUTS_REBIND (0, default): the
                               graph's kernel nodes are rewritten in place with the call's pointers
-                              when they differ from the ones it holds (the host first waits for that
-                              graph's previous replay to finish); a different launch shape (token
-                              count, dtype, alignment class) captures it again.
+                              when they differ from the ones it holds (for a graph replayed by
+                              hipGraphLaunch the host first waits for its previous replay to finish);
+                              a different launch shape (token count, dtype, alignment class) captures it again.
                               QE_GRAPH_INPUTS_RECAPTURE (1): captured again on any change.
                               QE_GRAPH_INPUTS_COPY (2): the paper's scheme: graphs bind static
                               library buffers (max_tokens rows of FP32 for X, Y, dY, dX per layer);
@@ -475,9 +478,9 @@ typedef struct {
   int64_t token;             /* host effect token: +1 per F and per dI */
   int64_t device_token;      /* last value read back by qe_sync (-1 if never) */
   int32_t arena_valid, finalized;
-  int64_t graphs;            /* graph executables held */
+  int64_t graphs;            /* graphs held */
   int64_t captures;          /* captures performed (prebuilt ones, first uses and re-captures) */
-  int64_t replays;           /* graph launches */
+  int64_t replays;           /* graph replays */
   int64_t handoffs;          /* caller<->graph stream handoffs (2 per action; 0 with replay_on_caller) */
   int64_t capture_ns;        /* host time spent capturing + instantiating */
   int64_t arena_bytes;       /* bytes covered by bound views */
