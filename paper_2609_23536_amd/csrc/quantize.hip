@@ -9,14 +9,15 @@
 // Q rounds to nearest even and saturates to +-fmax; NaN becomes 0x7F with the
 // input's sign bit.  Formats: OCP E4M3 (max 448) and E5M2 (max 57344).
 //
-// Layout: one workgroup of 256 lanes per 128 x 128 tile.  Phase 1: every load
+// Layout: one workgroup of 256 lanes per tile of 128 rows (64 for small tensors)
+// x 128 columns.  Phase 1: every load
 // instruction is one contiguous 16-byte piece per lane along a row (16 lanes
 // per bf16 row, 32 per fp32 row); each lane converts its 8 (or 4) values and
 // stores the codes row-wise and into an LDS tile whose 16-byte chunks are
 // XOR-swizzled by row block.
-// Phase 2: each lane gathers a 16-row x 4-column block of codes from LDS and
-// writes four 16-byte column segments; eight consecutive lanes complete one
-// 128-byte run of a transposed row.  amax: a max over the |x| bit patterns
+// Phase 2: each lane gathers a 16-row (8-row) x 4-column block of codes from LDS
+// and writes four 16-byte (8-byte) column segments; eight consecutive lanes
+// complete one 128-byte (64-byte) run of a transposed row.  amax: a max over the |x| bit patterns
 // (which order like the values, NaN above inf) per lane, a wave shuffle
 // reduction, then one atomicMax per workgroup into one of the 64 lines of the
 // role's amax accumulator (same-line atomics serialise).  HBM-bound: per element it
@@ -80,8 +81,10 @@ __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as
 
 __device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
+// A lane of phase 2 reads RPL consecutive rows; the swizzle follows its block.
+template <int RPL>
 __device__ __forceinline__ uint32_t lds_chunk_offset(int row, int chunk) {
-  return uint32_t(row) * kTile + (uint32_t((chunk ^ (row >> 4)) & 7) << 4);
+  return uint32_t(row) * kTile + (uint32_t((chunk ^ (row / RPL)) & 7) << 4);
 }
 
 __device__ __forceinline__ uint32_t byte_of(uint32_t w, int j) { return (w >> (8 * j)) & 0xffu; }
@@ -116,22 +119,23 @@ struct QuantPair {
 };
 
 // CUR: the cast of a current-scaling role derives its own scale (see scale_of).
-template <bool BF16, int FMT, bool CUR>
+template <bool BF16, int FMT, bool CUR, int ROWS>
 __device__ __forceinline__ void quantize_body(const QuantPair &pp, const CurrentParams &cp) {
-  __shared__ __attribute__((aligned(16))) uint8_t tile[kTile * kTile];
+  __shared__ __attribute__((aligned(16))) uint8_t tile[ROWS * kTile];
   __shared__ uint32_t red[kThreads / 64];
   // Phase 1 mapping: one 16-byte load per lane per step, consecutive lanes on
   // consecutive 16 bytes of a row (LPR lanes per 128-element row).
   constexpr int EPL = BF16 ? 8 : 4;          // elements per load
   constexpr int LPR = kTile / EPL;           // lanes per tile row
-  constexpr int NLD = kTile * kTile / (EPL * kThreads);  // loads per lane
+  constexpr int NLD = ROWS * kTile / (EPL * kThreads);  // loads per lane
+  constexpr int RPL = ROWS / 8;              // rows per lane in phase 2
   const int tid = threadIdx.x;
   const bool second = pp.n > 1 && int64_t(blockIdx.x) >= pp.j[0].tiles;  // uniform per workgroup
   const QuantJob &job = second ? pp.j[1] : pp.j[0];
   const QuantParams &p = job.p;
   const int64_t tiles_c = job.tiles_c;
   const int64_t t = second ? int64_t(blockIdx.x) - pp.j[0].tiles : int64_t(blockIdx.x);
-  const int64_t r0 = (t / tiles_c) * kTile;
+  const int64_t r0 = (t / tiles_c) * ROWS;
   const int64_t c0 = (t % tiles_c) * kTile;
   // The scale.  Under CUR every workgroup reduces the amax pass's partial
   // maxima (at most kMaxPartials floats, from the L2) instead of waiting for
@@ -173,7 +177,7 @@ __device__ __forceinline__ void quantize_body(const QuantPair &pp, const Current
     }
   };
   const float scale = scale_of();
-  const bool full = r0 + kTile <= p.rows && c0 + kTile <= p.cols;
+  const bool full = r0 + ROWS <= p.rows && c0 + kTile <= p.cols;
   uint32_t amax = 0;
 
   // Phase 1, for whole tiles (EDGE false) and tiles at the tensor's edge: a
@@ -257,7 +261,7 @@ __device__ __forceinline__ void quantize_body(const QuantPair &pp, const Current
       for (int u = 0; u < G; ++u) {
         const int q = (g + u) * kThreads + tid, row = q / LPR, cl = q % LPR;
         const int col = cl * EPL;
-        uint8_t *lds = tile + lds_chunk_offset(row, col >> 4) + (col & 15);
+        uint8_t *lds = tile + lds_chunk_offset<RPL>(row, col >> 4) + (col & 15);
         if constexpr (BF16)
           *reinterpret_cast<uint2 *>(lds) = make_uint2(codes[u][0], codes[u][1]);
         else
@@ -298,35 +302,33 @@ __device__ __forceinline__ void quantize_body(const QuantPair &pp, const Current
   }
 
   if (p.q_col == nullptr) return;
-  // Phase 2: lane (rb, cq) transposes rows rb*16..+16 x columns 4cq..4cq+3.
+  // Phase 2: lane (rb, cq) transposes RPL rows from rb*RPL x columns 4cq..4cq+3.
   const int rb = tid & 7, cq = tid >> 3;
-  uint32_t d[16];
+  uint32_t d[RPL];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int R = rb * 16 + i;
-    d[i] = *reinterpret_cast<const uint32_t *>(tile + lds_chunk_offset(R, cq >> 2) + ((cq & 3) << 2));
+  for (int i = 0; i < RPL; ++i) {
+    const int R = rb * RPL + i;
+    d[i] = *reinterpret_cast<const uint32_t *>(tile + lds_chunk_offset<RPL>(R, cq >> 2) + ((cq & 3) << 2));
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    uint32_t w[4];
+    uint32_t w[RPL / 4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < RPL / 4; ++q)
       w[q] = byte_of(d[4 * q], j) | (byte_of(d[4 * q + 1], j) << 8) | (byte_of(d[4 * q + 2], j) << 16) |
              (byte_of(d[4 * q + 3], j) << 24);
     const int64_t col = c0 + 4 * cq + j;
-    const int64_t rbase = r0 + rb * 16;
+    const int64_t rbase = r0 + rb * RPL;
     uint8_t *dst = p.q_col + col * p.ld_col + rbase;
-    if (full) {
-      *reinterpret_cast<u32x4_out *>(dst) = u32x4_out{w[0], w[1], w[2], w[3]};
-      continue;
-    }
-    if (col >= p.cols) continue;
-    if (rbase + 16 <= p.rows) {
-      *reinterpret_cast<u32x4_out *>(dst) = u32x4_out{w[0], w[1], w[2], w[3]};
-    } else {  // the last rows: whole words, then bytes
-      const int n = int(p.rows - rbase);
+    if (full || (col < p.cols && rbase + RPL <= p.rows)) {
+      if constexpr (RPL == 16)
+        *reinterpret_cast<u32x4_out *>(dst) = u32x4_out{w[0], w[1], w[2], w[3]};
+      else
+        *reinterpret_cast<u32x2_out *>(dst) = u32x2_out{w[0], w[1]};
+    } else if (col < p.cols) {  // the last rows: whole words, then bytes
+      const int64_t n = p.rows - rbase;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < RPL / 4; ++q) {
         if (4 * q + 4 <= n) {
           *reinterpret_cast<u32_out *>(dst + 4 * q) = w[q];
         } else {
@@ -339,49 +341,74 @@ __device__ __forceinline__ void quantize_body(const QuantPair &pp, const Current
   }
 }
 
-template <bool BF16, int FMT>
+template <bool BF16, int FMT, int ROWS>
 __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantPair pp) {
-  quantize_body<BF16, FMT, false>(pp, CurrentParams{});
+  quantize_body<BF16, FMT, false, ROWS>(pp, CurrentParams{});
 }
 
-template <bool BF16, int FMT>
+template <bool BF16, int FMT, int ROWS>
 __global__ __launch_bounds__(kThreads) void quantize_current_kernel(QuantPair pp, CurrentParams cp) {
-  quantize_body<BF16, FMT, true>(pp, cp);
+  quantize_body<BF16, FMT, true, ROWS>(pp, cp);
 }
 
-template <bool BF16>
-hipError_t launch_fmt(const QuantPair &pp, int fmt, hipStream_t s) {
-  int64_t tiles = 0;
-  for (int i = 0; i < pp.n; ++i) tiles += pp.j[i].tiles;
-  if (fmt == 0) return klaunch(quantize_kernel<BF16, 0>, dim3(unsigned(tiles)), dim3(kThreads), 0, s, pp);
-  return klaunch(quantize_kernel<BF16, 1>, dim3(unsigned(tiles)), dim3(kThreads), 0, s, pp);
+int64_t tiles_of(const QuantParams &p, int rows) {
+  const int64_t n = ((p.rows + rows - 1) / rows) * ((p.cols + kTile - 1) / kTile);
+  return n < 1 ? 1 : n;  // an empty tensor still writes the scale_inv snapshot
 }
 
-QuantJob make_job(const QuantParams &p) {
+QuantJob make_job(const QuantParams &p, int rows) {
   QuantJob j;
   memset(&j, 0, sizeof(j));  // padding too: recorded launches are compared bytewise
   j.p = p;
-  const int64_t tiles_r = (p.rows + kTile - 1) / kTile;
   const int64_t tiles_c = (p.cols + kTile - 1) / kTile;
-  j.tiles = tiles_r * tiles_c;
-  if (j.tiles < 1) j.tiles = 1;  // still writes the scale_inv snapshot
+  j.tiles = tiles_of(p, rows);
   j.tiles_c = tiles_c < 1 ? 1 : tiles_c;
   return j;
 }
 
-hipError_t launch_pair(const QuantPair &pp, hipStream_t s) {
-  return pp.j[0].p.in_bf16 ? launch_fmt<true>(pp, pp.j[0].p.fmt, s) : launch_fmt<false>(pp, pp.j[0].p.fmt, s);
+template <int ROWS>
+hipError_t launch_rows(const QuantParams *p, int n, const CurrentParams *cp, hipStream_t s) {
+  QuantPair pp;
+  memset(&pp, 0, sizeof(pp));
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    pp.j[i] = make_job(p[i], ROWS);
+    tiles += pp.j[i].tiles;
+  }
+  pp.n = n;
+  const dim3 grid{unsigned(tiles)}, block(kThreads);
+  const bool e4m3 = p[0].fmt == 0;
+  if (cp != nullptr) {
+    if (p[0].in_bf16)
+      return e4m3 ? klaunch(quantize_current_kernel<true, 0, ROWS>, grid, block, 0, s, pp, *cp)
+                  : klaunch(quantize_current_kernel<true, 1, ROWS>, grid, block, 0, s, pp, *cp);
+    return e4m3 ? klaunch(quantize_current_kernel<false, 0, ROWS>, grid, block, 0, s, pp, *cp)
+                : klaunch(quantize_current_kernel<false, 1, ROWS>, grid, block, 0, s, pp, *cp);
+  }
+  if (p[0].in_bf16)
+    return e4m3 ? klaunch(quantize_kernel<true, 0, ROWS>, grid, block, 0, s, pp)
+                : klaunch(quantize_kernel<true, 1, ROWS>, grid, block, 0, s, pp);
+  return e4m3 ? klaunch(quantize_kernel<false, 0, ROWS>, grid, block, 0, s, pp)
+              : klaunch(quantize_kernel<false, 1, ROWS>, grid, block, 0, s, pp);
+}
+
+// Up to two 128-row tiles per compute unit the tiles take 64 rows: twice the
+// workgroups, half the chain of loads and edge guards in each.  Measured on
+// MI355X (us, 128 rows -> 64): fp32 1000 x 2730 10.3 -> 7.6, 1500 x 4099 12.8 ->
+// 11.8, 2048 x 4096 (512 tiles) 11.7 -> 11.0; bf16 1000 x 2730 8.5 -> 7.7,
+// 2048 x 4096 level; one step of the 1365 x 2730 layer above 141 -> 131.  Beyond, the 64-byte runs of the transposed codes cost
+// more: bf16 4096 x 14336 46 -> 50, 57344 x 8192 321 -> 335, fp32 495 -> 554.
+constexpr int64_t kSmallTiles = 512;
+
+hipError_t launch_casts(const QuantParams *p, int n, const CurrentParams *cp, hipStream_t s) {
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += tiles_of(p[i], kTile);
+  return tiles <= kSmallTiles ? launch_rows<64>(p, n, cp, s) : launch_rows<kTile>(p, n, cp, s);
 }
 
 }  // namespace
 
-hipError_t launch_quantize(const QuantParams &p, hipStream_t s) {
-  QuantPair pp;
-  memset(&pp, 0, sizeof(pp));
-  pp.j[0] = make_job(p);
-  pp.n = 1;
-  return launch_pair(pp, s);
-}
+hipError_t launch_quantize(const QuantParams &p, hipStream_t s) { return launch_casts(&p, 1, nullptr, s); }
 
 hipError_t launch_quantize_current(const AmaxParams &a, const QuantParams &q, const MetaRef &m, long long *token,
                                    float *partials, hipStream_t s) {
@@ -394,18 +421,8 @@ hipError_t launch_quantize_current(const AmaxParams &a, const QuantParams &q, co
   cp.partials = partials;
   cp.n = amax_blocks(ap);
   cp.token = token;
-  QuantPair pp;
-  memset(&pp, 0, sizeof(pp));
-  pp.j[0] = make_job(q);
-  pp.n = 1;
   const hipError_t e = launch_amax(ap, s);
-  if (e != hipSuccess) return e;
-  const dim3 grid{unsigned(pp.j[0].tiles)}, block(kThreads);
-  if (q.in_bf16)
-    return q.fmt == 0 ? klaunch(quantize_current_kernel<true, 0>, grid, block, 0, s, pp, cp)
-                      : klaunch(quantize_current_kernel<true, 1>, grid, block, 0, s, pp, cp);
-  return q.fmt == 0 ? klaunch(quantize_current_kernel<false, 0>, grid, block, 0, s, pp, cp)
-                    : klaunch(quantize_current_kernel<false, 1>, grid, block, 0, s, pp, cp);
+  return e != hipSuccess ? e : launch_casts(&q, 1, &cp, s);
 }
 
 hipError_t launch_quantize_pair(const QuantParams &a, const QuantParams &b, hipStream_t s) {
@@ -413,12 +430,8 @@ hipError_t launch_quantize_pair(const QuantParams &a, const QuantParams &b, hipS
     const hipError_t e = launch_quantize(a, s);
     return e != hipSuccess ? e : launch_quantize(b, s);
   }
-  QuantPair pp;
-  memset(&pp, 0, sizeof(pp));
-  pp.j[0] = make_job(a);
-  pp.j[1] = make_job(b);
-  pp.n = 2;
-  return launch_pair(pp, s);
+  const QuantParams p[2] = {a, b};
+  return launch_casts(p, 2, nullptr, s);
 }
 
 }  // namespace qe

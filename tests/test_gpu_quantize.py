@@ -120,11 +120,12 @@ def test_padded_leading_dimensions_untouched():
 
 
 @pytest.mark.parametrize("shape", [(1, 3), (3, 1), (16, 7), (17, 8), (127, 129), (128, 131), (129, 128), (143, 255),
-                                   (252, 261), (272, 264)])
+                                   (63, 65), (65, 64), (252, 261), (272, 264), (2048, 4097), (2913, 2951)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_edge_tiles_unaligned(shape, dtype, shift):
-    """Edges of tiles and of 16-byte pieces in both directions, with the input one element and the outputs
+    """Edges of tiles and of 16-byte pieces in both directions, of 64-row tiles and (the last two shapes, more
+    than 512 of them) of 128-row tiles, with the input one element and the outputs
     one byte off every larger alignment; NaNs sit in the last row and column, and nothing outside the
     codes is written."""
     qe = need_lib()
