@@ -22,9 +22,9 @@ namespace qe {
 // 256 x 224 0.978.
 constexpr double kLargeF[3] = {14.0, 9.0, 25.0};  // by GemmParams::out: FP32, BF16, accumulate
 constexpr double kLargeF2 = 28.0;                 // accumulate, more than one round
-// added to F where rows are not vector-aligned: the checked epilogue's single
-// elements (2730 x 1365 x 1000: FP32 34, accumulate 78)
-constexpr double kLargeScalar[3] = {12.0, 12.0, 42.0};
+// added to F where rows are not vector-aligned: the checked epilogue (8191 x
+// 8191 x 2049, four rounds: FP32 181, accumulate 260)
+constexpr double kLargeScalar[3] = {11.0, 8.0, 17.0};
 constexpr double kCost256x192 = 0.89;
 constexpr double kCost192x256 = 0.86;
 constexpr double kCost224 = 0.98;
@@ -42,10 +42,10 @@ struct SmallTile {
   double f, s, s_k, s_deep, e[3], scalar;  // s + s_k * T per K tile
 };
 constexpr SmallTile kSmall[] = {
-    {kTile64x64, 0, 64, 64, 3.0, 0.19, 0.0, 0.0, {0.6, 0.3, 1.2}, 1.2},
-    {kTile128x64, kTile128x64Deep, 128, 64, 3.5, 0.30, 0.0, 0.295, {1.2, 0.5, 2.4}, 2.4},
-    {kTile64x128, kTile64x128Deep, 64, 128, 3.5, 0.30, 0.0, 0.295, {1.2, 0.5, 2.4}, 2.4},
-    {kTile128x128, kTile128x128Deep, 128, 128, 4.0, 0.46, 0.0008, 0.52, {2.2, 0.6, 5.6}, 4.8},
+    {kTile64x64, 0, 64, 64, 3.0, 0.19, 0.0, 0.0, {0.6, 0.3, 1.2}, 0.2},
+    {kTile128x64, kTile128x64Deep, 128, 64, 3.5, 0.30, 0.0, 0.295, {1.2, 0.5, 2.4}, 0.4},
+    {kTile64x128, kTile64x128Deep, 64, 128, 3.5, 0.30, 0.0, 0.295, {1.2, 0.5, 2.4}, 0.4},
+    {kTile128x128, kTile128x128Deep, 128, 128, 4.0, 0.46, 0.0008, 0.52, {2.2, 0.6, 5.6}, 0.8},
 };
 
 static std::atomic<int> g_tile_override{0};

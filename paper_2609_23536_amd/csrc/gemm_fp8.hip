@@ -381,8 +381,10 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
           const int64_t row = m0 + wm * TM + i * 32 + 2 * it + (lane >> 5);
           const int64_t col = n0 + wn * TN + (lane & 31) * 4;
           pre[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (has_col && row < M && vec_ok && (nfull || col + 4 <= N))
-            pre[it] = *reinterpret_cast<const float4 *>(static_cast<const float *>(g.c) + row * g.ldc + col);
+          if (has_col && row < M && (nfull || col + 4 <= N)) {
+            const v4f_out w = *reinterpret_cast<const v4f_out *>(static_cast<const float *>(g.c) + row * g.ldc + col);
+            pre[it] = make_float4(w[0], w[1], w[2], w[3]);
+          }
         }
       }
     }
@@ -456,17 +458,17 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
       const float4 v4 = *reinterpret_cast<const float4 *>(ep + r * EP + cl);
       if (row >= M) continue;
       const float v[4] = {v4.x, v4.y, v4.z, v4.w};
-      if (vec_ok && (nfull || col + 4 <= N)) {
+      if (nfull || col + 4 <= N) {  // at any alignment
         if constexpr (OUT == 0) {
-          *reinterpret_cast<float4 *>(static_cast<float *>(g.c) + row * g.ldc + col) = v4;
+          *reinterpret_cast<v4f_out *>(static_cast<float *>(g.c) + row * g.ldc + col) = v4f_out{v[0], v[1], v[2], v[3]};
         } else if constexpr (OUT == 1) {
           const uint32_t lo = bf16x2_bits(v[0], v[1]);
           const uint32_t hi = bf16x2_bits(v[2], v[3]);
-          *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(g.c) + row * g.ldc + col) = make_uint2(lo, hi);
+          *reinterpret_cast<v2i_out *>(static_cast<uint16_t *>(g.c) + row * g.ldc + col) = v2i_out{int(lo), int(hi)};
         } else {
           const float4 o = pre[it];
-          *reinterpret_cast<float4 *>(static_cast<float *>(g.c) + row * g.ldc + col) =
-              make_float4(o.x + v[0], o.y + v[1], o.z + v[2], o.w + v[3]);
+          *reinterpret_cast<v4f_out *>(static_cast<float *>(g.c) + row * g.ldc + col) =
+              v4f_out{o.x + v[0], o.y + v[1], o.z + v[2], o.w + v[3]};
         }
       } else {
 #pragma unroll

@@ -10,6 +10,11 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+// Output vectors at element alignment: global accesses are the same single
+// instructions at any address (unaligned access is the device's normal mode),
+// so rows of odd strides are written like aligned ones.
+typedef float v4f_out __attribute__((ext_vector_type(4), aligned(4)));
+typedef int v2i_out __attribute__((ext_vector_type(2), aligned(2)));
 
 constexpr int BK = 128;
 // Tiles are numbered down groups of kGroupM row tiles, column after column,
@@ -76,8 +81,8 @@ __device__ __forceinline__ int xcd_remap(int wg, int total) {
 
 }  // namespace
 
-// Destinations the kernels can write with vector stores (BF16: 8 bytes, FP32:
-// 16 bytes per lane).
+// Destinations whose rows are vector-aligned (BF16: 8 bytes, FP32: 16 bytes per
+// lane): the branch-free epilogue of the large tiles takes only these.
 inline int gemm_vec_ok(const GemmParams &g) {
   const uintptr_t cp = reinterpret_cast<uintptr_t>(g.c);
   return g.ldc % 4 == 0 && cp % (g.out == 1 ? 8 : 16) == 0 ? 1 : 0;

@@ -440,3 +440,32 @@ def test_seeded_shape_sweep_exact(shape):
     assert torch.equal(cb.view(torch.bfloat16), ref.float().to(torch.bfloat16))
     assert torch.equal(ca[:, :n], (base[:, :n].double() + ref).float())
     assert torch.equal(ca[:, n:], base[:, n:])
+
+
+@pytest.mark.parametrize("shape", [(70, 61, 200), (257, 1000, 100), (300, 258, 130), (129, 515, 64), (3000, 4099, 96)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("out", ["f32", "bf16", "accumulate"])
+def test_destination_at_element_alignment(forced_tile, shape, out):
+    """The destination starts one element past every vector alignment and its rows have an odd stride: every
+    tile shape stores the exact integer product (BF16: rounded once), column counts of every remainder by
+    four, and no other element."""
+    qe = forced_tile
+    d = dev()
+    m, n, k = shape
+    ai, bi, a_t, b_t = _int_operands(d, m, n, k, k + 5)
+    lda = a_t.shape[1]
+    s = torch.tensor([1.0, 1.0], dtype=torch.float32, device=d)
+    ldc = n + 1 + n % 2
+    tdt = torch.bfloat16 if out == "bf16" else torch.float32
+    base = torch.randint(-50, 50, (1 + m * ldc + 8,), device=d, generator=torch.Generator(device=d).manual_seed(n)).to(tdt)
+    want = base.clone()
+    view = want[1:1 + m * ldc].view(m, ldc)[:, :n]
+    ref = (ai.double() @ bi.double().T).to(tdt)
+    view.copy_(view + ref if out == "accumulate" else ref)
+    for tile in (0, 1, 2, 3, 4, 5):
+        assert qe.qe_set_gemm_tile(tile) == "OK"
+        c = base.clone()
+        assert qe.qe_fp8_gemm_tn(a_t, 0, lda, b_t, 0, lda, m, n, k, s[0:1], s[1:2], c[1:],
+                                 qe.BF16 if out == "bf16" else qe.F32, ldc,
+                                 qe.ACCUM if out == "accumulate" else qe.INIT) == "OK"
+        assert torch.equal(c, want), tile
