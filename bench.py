@@ -8,11 +8,11 @@ master weights, amax history 1024):  F (with the weight-cache refresh, since
 every step follows a version bump), then dI and the deferred dW with direct
 placement into one flat FP32 main-gradient buffer, then arena finalize and
 optimizer commit.  The stage's graphs are captured before the first step
-(qe_prebuild_graphs) and every action is one HIP-graph replay, by default on
-the caller's stream (stream order gives both directions of the handoff;
---executor two-way runs the paper's two-way handoff through the library's
-graph stream instead, and the line reports the other executor's step time
-beside the headline).  Inputs are synthetic, seeded, and resident in HBM
+(qe_prebuild_graphs) and every action replays its graph (chains as short as
+these are replayed launch by launch), by default on the caller's stream
+(stream order gives both directions of the handoff; --executor two-way runs
+the paper's two-way handoff through the library's graph stream instead, and
+the line reports the other executor's step time beside the headline).  Inputs are synthetic, seeded, and resident in HBM
 before timing starts.
 
 Prints one JSON line.  `value` is GEMM FLOPs (fwd + dI + dW, 2*M*N*K each)

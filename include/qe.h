@@ -209,13 +209,13 @@ qe_status qe_fp8_gemm_tn(const uint8_t *a, qe_fp8_fmt fmt_a, int64_t lda, const 
                          qe_stream stream);
 
 /* Macro-tile shape of every FP8 GEMM the library launches (qe_fp8_gemm_tn and
- * the layer actions).  QE_TILE_AUTO picks, per call, the shape that needs the
- * fewest rounds of workgroups over the device's compute units (256 on
- * MI355X, read from the device properties), weighted by a
- * measured per-round cost; the others force one shape (for tests and
- * measurements).  Process-wide; it applies to launches enqueued afterwards
+ * the layer actions).  QE_TILE_AUTO picks, per call, among these shapes and
+ * smaller ones (64x64 to 128x128) the one that a measured cost model of rounds
+ * of workgroups over the device's compute units (256 on MI355X, read from the
+ * device properties) expects to be fastest; the others force one shape (for
+ * tests and measurements).  Process-wide; it applies to launches enqueued afterwards
  * (a graph captured earlier keeps the shapes it was captured with).  The
- * five shapes give the same bits: the same 16x16x128 MFMA with the same
+ * shapes all give the same bits: the same 16x16x128 MFMA with the same
  * reduction bytes per lane, the same order along K, no split reduction.
  * Errors: QE_ERR_INVALID_ARG for a value outside the enum. */
 typedef enum {
