@@ -182,8 +182,13 @@ __device__ __forceinline__ void quantize_body(const QuantPair &pp, const Current
 
   // Phase 1, for whole tiles (EDGE false) and tiles at the tensor's edge: a
   // lane's elements past the last column or row count as zero and are not
-  // stored.  Edge tiles take their steps in two groups, so that their guards
-  // cost the whole tiles no registers.
+  // stored.  Edge tiles take their steps in two groups; both paths share one
+  // register allocation (128 rows: bf16 145 VGPRs and 26 scalars kept in VGPR
+  // lanes, fp32 134, three waves per SIMD).  Four groups take bf16 to 144 and
+  // no such scalars, which whole tiles do not notice (4096 x 4096 15.3 us
+  // either way) and edge tiles do (8192 x 8208 57.3 -> 58.7, 5000 x 4099 21.5
+  // -> 22.1); fp32 held to 128 VGPRs for a fourth wave is slower (4096 x 4096
+  // 22.5 -> 23.0, with its scale update).
   auto cast_tile = [&](auto edge) {
     constexpr bool EDGE = decltype(edge)::value;
     // valid elements of the lane's piece of step `it`
@@ -303,6 +308,8 @@ __device__ __forceinline__ void quantize_body(const QuantPair &pp, const Current
 
   if (p.q_col == nullptr) return;
   // Phase 2: lane (rb, cq) transposes RPL rows from rb*RPL x columns 4cq..4cq+3.
+  // Whole tiles have a loop of their own, without the guards (bf16 4096 x 4096,
+  // in one run with a common loop: 15.35 -> 15.00 us, fp32 8192 x 8192 65.4 -> 65.2).
   const int rb = tid & 7, cq = tid >> 3;
   uint32_t d[RPL];
 #pragma unroll
@@ -310,23 +317,37 @@ __device__ __forceinline__ void quantize_body(const QuantPair &pp, const Current
     const int R = rb * RPL + i;
     d[i] = *reinterpret_cast<const uint32_t *>(tile + lds_chunk_offset<RPL>(R, cq >> 2) + ((cq & 3) << 2));
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    uint32_t w[RPL / 4];
+  auto segment = [&](int j, uint32_t *w) -> uint8_t * {
 #pragma unroll
     for (int q = 0; q < RPL / 4; ++q)
       w[q] = byte_of(d[4 * q], j) | (byte_of(d[4 * q + 1], j) << 8) | (byte_of(d[4 * q + 2], j) << 16) |
              (byte_of(d[4 * q + 3], j) << 24);
-    const int64_t col = c0 + 4 * cq + j;
-    const int64_t rbase = r0 + rb * RPL;
-    uint8_t *dst = p.q_col + col * p.ld_col + rbase;
-    if (full || (col < p.cols && rbase + RPL <= p.rows)) {
-      if constexpr (RPL == 16)
-        *reinterpret_cast<u32x4_out *>(dst) = u32x4_out{w[0], w[1], w[2], w[3]};
-      else
-        *reinterpret_cast<u32x2_out *>(dst) = u32x2_out{w[0], w[1]};
-    } else if (col < p.cols) {  // the last rows: whole words, then bytes
-      const int64_t n = p.rows - rbase;
+    return p.q_col + (c0 + 4 * cq + j) * p.ld_col + r0 + rb * RPL;
+  };
+  auto store = [](uint8_t *dst, const uint32_t *w) {
+    if constexpr (RPL == 16)
+      *reinterpret_cast<u32x4_out *>(dst) = u32x4_out{w[0], w[1], w[2], w[3]};
+    else
+      *reinterpret_cast<u32x2_out *>(dst) = u32x2_out{w[0], w[1]};
+  };
+  if (full) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t w[RPL / 4];
+      uint8_t *dst = segment(j, w);
+      store(dst, w);
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t w[RPL / 4];
+    uint8_t *dst = segment(j, w);
+    if (c0 + 4 * cq + j >= p.cols) continue;
+    const int64_t n = p.rows - (r0 + rb * RPL);
+    if (n >= RPL) {
+      store(dst, w);
+    } else {  // the last rows: whole words, then bytes
 #pragma unroll
       for (int q = 0; q < RPL / 4; ++q) {
         if (4 * q + 4 <= n) {
@@ -396,8 +417,9 @@ hipError_t launch_rows(const QuantParams *p, int n, const CurrentParams *cp, hip
 // workgroups, half the chain of loads and edge guards in each.  Measured on
 // MI355X (us, 128 rows -> 64): fp32 1000 x 2730 10.3 -> 7.6, 1500 x 4099 12.8 ->
 // 11.8, 2048 x 4096 (512 tiles) 11.7 -> 11.0; bf16 1000 x 2730 8.5 -> 7.7,
-// 2048 x 4096 level; one step of the 1365 x 2730 layer above 141 -> 131.  Beyond, the 64-byte runs of the transposed codes cost
-// more: bf16 4096 x 14336 46 -> 50, 57344 x 8192 321 -> 335, fp32 495 -> 554.
+// 2048 x 4096 level; one step of the 1365 x 2730 layer above 141 -> 131.
+// Beyond, the 64-byte runs of the transposed codes cost more: bf16 4096 x
+// 14336 46 -> 50, 57344 x 8192 321 -> 335, fp32 495 -> 554.
 constexpr int64_t kSmallTiles = 512;
 
 hipError_t launch_casts(const QuantParams *p, int n, const CurrentParams *cp, hipStream_t s) {
