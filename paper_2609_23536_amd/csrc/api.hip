@@ -442,29 +442,12 @@ hipError_t copy_all(const std::vector<Copy> &cs, hipStream_t s) {
   return hipSuccess;
 }
 
-// One action's kernel sequence, replayed from its graph (one per (layer,
-// action, slot)), or launched directly.  Graph-stream executor: the two-way
-// handoff around it (§2.3, §4.4).  replay_on_caller: launched on the caller's
-// stream, chained to the previous action through that action's completion
-// event.  `pre` / `post`: the dynamic-input copies of QE_GRAPH_INPUTS_COPY,
-// enqueued after the caller -> graph edge and before the completion event.
-qe_status run_plan(qe_ctx *c, const Plan &plan, uint64_t gkey, hipStream_t caller, const std::vector<Copy> &pre = {},
-                   const std::vector<Copy> &post = {}) {
-  DeviceGuard dg(c->cfg.device);
-  if (!dg.ok) return QE_ERR_HIP;
-  const bool on_caller = c->cfg.replay_on_caller != 0;
-  const hipStream_t s = on_caller ? caller : c->gs;
-  if (on_caller) {
-    // Stream order covers both directions of the handoff.  The wait on the
-    // previous action's event orders actions issued from different streams;
-    // on the same stream it is already satisfied by stream order.
-    if (c->has_last && hipStreamWaitEvent(caller, c->last_ev, 0) != hipSuccess) return QE_ERR_HIP;
-  } else if (caller != c->gs) {
-    if (hipEventRecord(c->ev_in, caller) != hipSuccess) return QE_ERR_HIP;
-    if (hipStreamWaitEvent(c->gs, c->ev_in, 0) != hipSuccess) return QE_ERR_HIP;
-  }
+// Enqueue one action's kernel sequence on s: replayed from its graph (one per
+// (layer, action, slot)), or launched directly, between its copies.  *done is
+// the event to record after it, whether or not all of it was enqueued.
+qe_status enqueue_action(qe_ctx *c, const Plan &plan, uint64_t gkey, hipStream_t s, const std::vector<Copy> &pre,
+                         const std::vector<Copy> &post, hipEvent_t *done) {
   if (copy_all(pre, s) != hipSuccess) return QE_ERR_HIP;
-  hipEvent_t done = on_caller ? c->ev_chain : c->ev_tail;
   if (c->cfg.use_graphs) {
     GraphEntry &e = c->graphs[gkey];
     const qe_status bs = bind_graph(c, e, plan);
@@ -480,20 +463,51 @@ qe_status run_plan(qe_ctx *c, const Plan &plan, uint64_t gkey, hipStream_t calle
     }
     e.launched = true;
     c->st.replays += 1;
-    done = e.done;  // the graph's own event: a rebind waits for exactly this replay
+    *done = e.done;  // the graph's own event: a rebind waits for exactly this replay
   } else {
     if (enqueue(c, plan, c->timing != 0, s) != hipSuccess) return QE_ERR_HIP;
   }
-  if (copy_all(post, s) != hipSuccess) return QE_ERR_HIP;
-  if (hipEventRecord(done, s) != hipSuccess) return QE_ERR_HIP;
+  return copy_all(post, s) == hipSuccess ? QE_OK : QE_ERR_HIP;
+}
+
+// One action.  Graph-stream executor: the two-way handoff around it (§2.3,
+// §4.4).  replay_on_caller: launched on the caller's stream, chained to the
+// previous action through that action's completion event.  `pre` / `post`: the
+// dynamic-input copies of QE_GRAPH_INPUTS_COPY, enqueued after the caller ->
+// graph edge and before the completion event.
+qe_status run_plan(qe_ctx *c, const Plan &plan, uint64_t gkey, hipStream_t caller, const std::vector<Copy> &pre = {},
+                   const std::vector<Copy> &post = {}) {
+  DeviceGuard dg(c->cfg.device);
+  if (!dg.ok) return QE_ERR_HIP;
+  const bool on_caller = c->cfg.replay_on_caller != 0;
+  const hipStream_t s = on_caller ? caller : c->gs;
+  if (on_caller) {
+    // Stream order covers both directions of the handoff.  The wait on the
+    // previous action's event orders actions issued from different streams;
+    // on the same stream it is already satisfied by stream order.
+    if (c->has_last && hipStreamWaitEvent(caller, c->last_ev, 0) != hipSuccess) return QE_ERR_HIP;
+  } else if (caller != c->gs) {
+    if (hipEventRecord(c->ev_in, caller) != hipSuccess) return QE_ERR_HIP;
+    if (hipStreamWaitEvent(c->gs, c->ev_in, 0) != hipSuccess) return QE_ERR_HIP;
+  }
+  hipEvent_t done = on_caller ? c->ev_chain : c->ev_tail;
+  const qe_status st = enqueue_action(c, plan, gkey, s, pre, post, &done);
+  // An action that failed part-way has kernels in flight too: it gets its
+  // completion event and its way back to the caller like a whole one, so that
+  // the next action, the caller and sync_actions come after them.  Without
+  // the event only the host can wait.
+  if (hipEventRecord(done, s) != hipSuccess) {
+    (void)hipStreamSynchronize(s);
+    return QE_ERR_HIP;
+  }
   c->last_ev = done;
   c->has_last = true;
-  if (on_caller) return QE_OK;
+  if (on_caller) return st;
   if (!c->cfg.one_way_handoff && caller != c->gs) {
     if (hipStreamWaitEvent(caller, done, 0) != hipSuccess) return QE_ERR_HIP;
   }
-  c->st.handoffs += 2;
-  return QE_OK;
+  if (st == QE_OK) c->st.handoffs += 2;
+  return st;
 }
 
 uint64_t graph_key(int layer, int action, uint32_t slot) {
