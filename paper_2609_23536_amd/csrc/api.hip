@@ -51,15 +51,21 @@ namespace {
 int64_t rup16(int64_t v) { return (v + 15) / 16 * 16; }
 
 // Row stride of the library's own code buffers, for rows of v codes: whole
-// 128-byte lines.  The GEMM loads 128-byte row pieces, and rows that start
-// inside a line make each piece two lines.  Measured on MI355X, 8192^3 with
-// strides of 8192 + 0 / 16 / 64 / 128: 395 / 472 / 435 / 379 us; 512 x 4096 x
-// 14336: 36.6 / 59.2 / 44.9 / 35.9; one step of a 1365 x 2730 layer with two
-// 1000-token microbatches 151 us with strides rounded to 16, 141 so.  (An odd
-// number of lines for long rows, 128 bytes more, gains on repeated products of
-// the same operands and nothing over a step: 818 and 2400 us against 818 and
-// 2409.)
-int64_t code_ld(int64_t v) { return (v + 127) / 128 * 128; }
+// 128-byte lines for rows of more than 256.  The GEMM loads 128-byte row
+// pieces, and rows that start inside a line make each piece two lines.
+// Measured on MI355X, 8192^3 with strides of 8192 + 0 / 16 / 64 / 128: 395 /
+// 472 / 435 / 379 us; 512 x 4096 x 14336: 36.6 / 59.2 / 44.9 / 35.9; one step
+// of a 1365 x 2730 layer with two 1000-token microbatches 151 us with strides
+// rounded to 16, 141 so.  (An odd number of lines for long rows, 128 bytes more,
+// gains on repeated products of the same operands and nothing over a step: 818
+// and 2400 us against 818 and 2409.)
+// Shorter rows, the transposed codes of small microbatches, are rounded to 16
+// only: a K loop of one or two tiles has little to lose and the slots would take
+// up to eight times the memory (6144 x 4096 x K, stride rounded to 16 / 128, us:
+// K 16 to 112 level, 144 24.8 / 25.0, 208 25.7 / 25.0, then 272 28.5 / 26.8,
+// 528 34.0 / 31.3, 1040 47.2 / 39.9).  Above, the cost is at most 112 bytes a
+// row: 41% at 257 codes, 11% from 1025 on.
+int64_t code_ld(int64_t v) { return v <= 256 ? rup16(v) : (v + 127) / 128 * 128; }
 
 // Device address of `scratch` on the current device, looked up once per
 // device (each device holds its own copy at its own address).

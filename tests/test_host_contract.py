@@ -387,3 +387,17 @@ def test_graph_inputs_mode_checked():
     for bad in (-1, 3):
         with pytest.raises(RuntimeError):
             qe.Context(1, use_graphs=True, null_executor=True, graph_inputs=bad)
+
+
+def test_code_buffers_of_short_rows_are_not_padded_to_lines():
+    """Rows of up to 256 codes (small microbatches, small layers) are rounded to 16 bytes, as the GEMM needs
+    them; longer ones to whole 128-byte lines."""
+    qe = need_lib()
+    for codes, ld in ((1, 16), (16, 16), (17, 32), (64, 64), (100, 112), (129, 144), (256, 256), (257, 384),
+                      (1000, 1024), (1365, 1408), (4096, 4096)):
+        c = qe.Context(1, null_executor=True)
+        st, layer = c.qe_layer_register(0, 0, codes, codes, codes, 0, qe.F32, 4, 0)
+        assert st == "OK"
+        slot, cache = c.qe_layer_slot_payload(layer, 0), c.qe_layer_cache(layer)
+        assert (slot["ld_x_q_t"], slot["ld_dy_q_t"], cache["ld_w_q"], cache["ld_w_q_t"]) == (ld,) * 4, codes
+        c.close()
