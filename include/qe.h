@@ -238,9 +238,11 @@ typedef struct {
   int32_t device;        /* HIP device ordinal */
   int32_t microbatches;  /* M: tape slots per layer, slot p = microbatch m */
   int32_t use_graphs;    /* 1: capture each (layer, action, slot) sequence once and replay it.  A captured
-                            chain of up to eight kernels (every action but those on products split at
-                            2 GiB) is replayed by enqueuing its launches on the stream, a longer one
-                            by hipGraphLaunch; order and results are the same. */
+                            chain of up to eight kernels is replayed by enqueuing its launches on the
+                            stream, a longer one by hipGraphLaunch; order and results are the same.
+                            (An action has two to five kernels, and one more for every 2 GiB block
+                            past the first of an operand of a product.)  2: as 1, with every chain
+                            instantiated and replayed by hipGraphLaunch. */
   int32_t null_executor; /* 1: run the contract only, no HIP call at all (host-only testing) */
   int32_t one_way_handoff; /* testing only: skip the caller's wait on the graph tail (§2.3) */
   int32_t copy_gradients;  /* 1: dW goes to a private FP32 buffer, then is copied into the bound view
@@ -258,10 +260,11 @@ typedef struct {
                               action of the graph-stream executor. */
   int32_t graph_inputs;     /* how a replayed graph meets the buffers of each call (§4.4, dynamic
                               inputs); use_graphs only.  QE_GRAPH_INPUTS_REBIND (0, default): the
-                              graph's kernel nodes are rewritten in place with the call's pointers
-                              when they differ from the ones it holds (for a graph replayed by
-                              hipGraphLaunch the host first waits for its previous replay to finish);
-                              a different launch shape (token count, dtype, alignment class) captures it again.
+                              graph's launches take the call's pointers in place when they differ
+                              from the ones it holds (in a graph replayed by hipGraphLaunch its
+                              kernel nodes are rewritten, after the host has waited for its previous
+                              replay); a different launch shape (token count, dtype, alignment
+                              class) captures it again.
                               QE_GRAPH_INPUTS_RECAPTURE (1): captured again on any change.
                               QE_GRAPH_INPUTS_COPY (2): the paper's scheme: graphs bind static
                               library buffers (max_tokens rows of FP32 for X, Y, dY, dX per layer);

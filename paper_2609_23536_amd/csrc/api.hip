@@ -6,11 +6,12 @@
 // graph stream.  The graph stream first waits on the caller's stream; the
 // action's kernel sequence is then either launched directly (eager) or
 // replayed from a graph captured once per (layer, action, slot) (§4.3, eq.
-// G_r: G = 3 M L graphs, which qe_prebuild_graphs captures up front; a short
-// chain's replay enqueues its launches, see kDirectReplay); finally
+// G_r: G = 3 M L graphs, which qe_prebuild_graphs captures up front; the replay
+// of a short chain enqueues the launches the graph was captured from, that of a
+// long one is a hipGraphLaunch, see kDirectReplay); finally
 // an event recorded right after the launch is waited on by the caller's
 // stream (the two-way handoff of §2.3).  The completion event is recorded by
-// hipEventRecord after hipGraphLaunch, never as an event-record node inside
+// hipEventRecord after the replay, never as an event-record node inside
 // the graph: on this runtime a stream waiting on an event that a graph node
 // records was measured not to wait for the graph's kernels (a consumer on the
 // caller's stream saw stale output in most trials), while a record enqueued
@@ -18,12 +19,12 @@
 //
 // Dynamic inputs (§4.4).  Graphs bind the buffers of the call they were
 // captured for.  When an action is called with other buffers, the default
-// (QE_GRAPH_INPUTS_REBIND) rewrites the arguments of the graph's kernel nodes
-// in place (hipGraphExecKernelNodeSetParams): every action's launches are
-// recorded on the host first (qe::klaunch in record mode) and compared with
-// the ones the graph holds, and only nodes whose argument bytes differ are
-// rewritten; a different launch shape (grid, kernel instance) captures the
-// graph again.  QE_GRAPH_INPUTS_COPY is the paper's scheme: graphs bind
+// (QE_GRAPH_INPUTS_REBIND) replaces the arguments in place: every action's
+// launches are recorded on the host first (qe::klaunch in record mode) and
+// compared with the ones the graph holds, and those whose argument bytes differ
+// are replaced in the recorded chain (a short one) or in the kernel nodes of the
+// executable (hipGraphExecKernelNodeSetParams); a different launch shape (grid,
+// kernel instance) captures the graph again.  QE_GRAPH_INPUTS_COPY is the paper's scheme: graphs bind
 // library-owned static buffers, and the caller's inputs are copied in before
 // the replay and the outputs copied out after it.  QE_GRAPH_INPUTS_RECAPTURE
 // captures the graph again on any change (for comparison).
@@ -180,12 +181,14 @@ struct GraphEntry {
 // launches on the stream one by one instead of by hipGraphLaunch, which takes
 // 20-22 us of host time whatever the graph holds and leaves the device idle
 // for 13.4 us between two actions, against 1.0-1.3 us a launch and 5.7 us.  An
-// action has two to five kernels; only products split at 2 GiB make more, and
-// near sixteen the two cost the same.  Measured on MI355X, both on one box: a
-// 4096 x 4096 layer with four 256-token microbatches behind the two-way handoff
-// 638 -> 474 us a step, 14336 x 4096 with two of 2048 tokens 830 -> 785, the
-// Llama-3-8B stage 2409 -> 2333, the Llama-3-70B stage 15500 -> 15384.
+// action has two to five kernels, one more for every 2 GiB block past the first
+// of a product's operand; near sixteen the two cost the same.  Measured on
+// MI355X, both on one box: a 4096 x 4096 layer with four 256-token microbatches
+// behind the two-way handoff 638 -> 474 us a step, 14336 x 4096 with two of 2048
+// tokens 830 -> 785, the Llama-3-8B stage 2409 -> 2333, the Llama-3-70B stage
+// 15500 -> 15384.  use_graphs = kUseExecutables instantiates every chain.
 constexpr size_t kDirectReplay = 8;
+constexpr int32_t kUseExecutables = 2;
 
 // A device-to-device copy around a replay (QE_GRAPH_INPUTS_COPY).
 struct Copy {
@@ -389,7 +392,7 @@ qe_status capture(qe_ctx *c, GraphEntry &e, const Plan &plan, std::vector<qe::Ke
          kp.sharedMemBytes == r.shmem;
   }
   e.rebindable = ok;
-  e.direct = ok && e.nodes.size() <= kDirectReplay;
+  e.direct = ok && c->cfg.use_graphs != kUseExecutables && e.nodes.size() <= kDirectReplay;
   if (!e.direct && hipGraphInstantiate(&e.exec, graph, nullptr, nullptr, 0) != hipSuccess) {
     e.exec = nullptr;
     (void)hipGraphDestroy(graph);

@@ -14,9 +14,10 @@ namespace qe {
 // functions below go through klaunch(), which either launches the kernel on a
 // stream or, while a recording list is installed on the calling thread,
 // appends the launch to it without touching the device.  The executor records
-// an action's launches to compare them with the kernel nodes of the graph it
-// captured earlier and to rewrite the arguments of those nodes in place when
-// only the arguments differ (hipGraphExecKernelNodeSetParams).
+// an action's launches to compare them with the ones it captured earlier.
+// Where only arguments differ it replaces those in place: in the recorded
+// chain it replays launch by launch, or in the kernel nodes of a longer
+// chain's executable (hipGraphExecKernelNodeSetParams).
 constexpr int kMaxKernelArgs = 8;
 constexpr int kKernelArgBytes = 1024;
 struct KernelRec {

@@ -229,7 +229,7 @@ def make_meta(hist, scale, scale_inv, fmt: int, margin: int = 0, amax_accum=None
 class Context:
     """Owns one qe_ctx.  Methods forward to the C calls of the same name."""
 
-    def __init__(self, microbatches: int, use_graphs: bool = False, null_executor: bool = False, device: int = 0,
+    def __init__(self, microbatches: int, use_graphs: int = False, null_executor: bool = False, device: int = 0,
                  one_way_handoff: bool = False, copy_gradients: bool = False, replay_on_caller: bool = False,
                  graph_inputs: int = GRAPH_INPUTS_REBIND):
         cfg = Config(device, microbatches, int(use_graphs), int(null_executor), int(one_way_handoff),

@@ -8,6 +8,7 @@ module; `calls` runs it in a child process and returns what it returns (JSON val
     def test_it(): assert calls(scenario) == ...
 """
 import ctypes as C
+import functools
 import importlib
 import json
 import os
@@ -26,7 +27,8 @@ class Hip:
         self.so.fake_log.restype = C.c_char_p
         self.so.fake_drain.argtypes = [C.c_void_p]
         self.pending, self.drain = self.so.fake_pending, self.so.fake_drain
-        self.fail_launch, self.fail_record, self.clear = self.so.fake_fail_launch, self.so.fake_fail_record, self.so.fake_clear
+        self.fail_launch, self.fail_record = self.so.fake_fail_launch, self.so.fake_fail_record
+        self.clear = self.so.fake_clear
 
     def log(self, *kinds):
         """The logged calls as lists of words; with kinds, those that begin with one of them."""
@@ -34,13 +36,19 @@ class Hip:
         return [w for w in lines if not kinds or w[0] in kinds]
 
 
+@functools.lru_cache(maxsize=None)
+def _built():
+    """The folder of the built runtime, removed with the process."""
+    td = tempfile.TemporaryDirectory()
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", SOURCE, "-o", os.path.join(td.name, "libfakehip.so")], check=True)
+    return td
+
+
 def calls(scenario, *args):
-    with tempfile.TemporaryDirectory() as td:
-        so = os.path.join(td, "libfakehip.so")
-        subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
-                        "-I/opt/rocm/include", SOURCE, "-o", so], check=True)
-        r = subprocess.run([sys.executable, "-m", "tests.fake_hip", so, scenario.__module__.split(".")[-1], scenario.__name__,
-                            json.dumps(args)], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    so = os.path.join(_built().name, "libfakehip.so")
+    r = subprocess.run([sys.executable, "-m", "tests.fake_hip", so, scenario.__module__.split(".")[-1],
+                        scenario.__name__, json.dumps(args)], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     return json.loads(r.stdout.splitlines()[-1])
 
@@ -49,4 +57,5 @@ if __name__ == "__main__":
     sys.modules["torch"] = None  # importing it fails
     hip = Hip(sys.argv[1])
     from paper_2609_23536_amd import qe
-    print(json.dumps(getattr(importlib.import_module("tests." + sys.argv[2]), sys.argv[3])(qe, hip, *json.loads(sys.argv[4]))))
+    scenario = getattr(importlib.import_module("tests." + sys.argv[2]), sys.argv[3])
+    print(json.dumps(scenario(qe, hip, *json.loads(sys.argv[4]))))

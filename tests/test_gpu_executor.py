@@ -56,7 +56,7 @@ def _same(a, b):
             assert x[r][1:] == y[r][1:]
 
 
-@pytest.mark.parametrize("use_graphs", [False, True], ids=["eager", "graphs"])
+@pytest.mark.parametrize("use_graphs", [False, True, 2], ids=["eager", "graphs", "executables"])
 def test_caller_stream_bitwise_equals_graph_stream(use_graphs):
     ref = _run(use_graphs, False)
     got = _run(use_graphs, True)
@@ -66,7 +66,7 @@ def test_caller_stream_bitwise_equals_graph_stream(use_graphs):
         assert got[4]["replays"] == ref[4]["replays"] > 0
 
 
-@pytest.mark.parametrize("use_graphs", [False, True], ids=["eager", "graphs"])
+@pytest.mark.parametrize("use_graphs", [False, True, 2], ids=["eager", "graphs", "executables"])
 def test_caller_stream_chains_actions_across_streams(use_graphs):
     """Every action on the next of three streams (F, dI and the deferred dW of
     one microbatch on different streams; scale updates in fixed order across

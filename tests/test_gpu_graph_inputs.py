@@ -192,3 +192,32 @@ def test_prebuilt_for_other_token_count_recaptures_once():
     _same(ref, got)
     G = 3 * M * len(SPEC.shapes)
     assert G < got[2]["captures"] <= 2 * G, got[2]
+
+
+# use_graphs = 2: every chain instantiated and replayed by hipGraphLaunch, its nodes rewritten in place
+EXECUTABLES = {
+    "rebind_graph_stream": dict(graph_inputs=0),
+    "rebind_caller_stream": dict(graph_inputs=0, replay_on_caller=True),
+    "recapture": dict(graph_inputs=1),
+    "copy": dict(graph_inputs=2),
+    "no_prebuild": dict(prebuild=False),
+    "other_token_count": dict(prebuild_tokens=SPEC.tokens - 72),
+    "current_scaling": dict(current=True),
+    "full_backward": dict(full=True),
+    "copied_gradients": dict(copy_gradients=True),
+}
+
+
+@pytest.mark.parametrize("variant", list(EXECUTABLES))
+def test_executables_with_rotating_buffers(variant):
+    """The rotations above on graph executables: the bits of direct launches, from the captures and rebinds that
+    the same program has with chains replayed launch by launch."""
+    qe = need_lib()
+    kw = EXECUTABLES[variant]
+    plain = {k: v for k, v in kw.items() if k not in ("graph_inputs", "prebuild", "prebuild_tokens")}
+    got = _run(qe, use_graphs=2, **kw)
+    _same(_run(qe, use_graphs=False, **plain), got)
+    direct = _run(qe, use_graphs=1, **kw)
+    for count in ("captures", "graphs", "replays", "rebinds", "rebound_nodes"):
+        assert got[2][count] == direct[2][count], count
+    assert got[2]["replays"] > 0

@@ -2,8 +2,8 @@
 row): with the two-way handoff a consumer enqueued on the caller stream right
 after a replayed action always sees the action's final output; with only the
 one-way edge (testing mode) it can observe stale data.  Checked with an
-explicit caller stream and with the default stream, graph replay and direct
-launches: a completion event recorded by a node inside the graph was found
+explicit caller stream and with the default stream, for direct launches,
+captured chains replayed launch by launch and graph executables: a completion event recorded by a node inside the graph was found
 not to order a waiting stream on this runtime, so the executor records it
 after the launch, and these trials are what shows that it orders."""
 import pytest
@@ -14,7 +14,7 @@ from tests.libqe import need_lib
 pytestmark = pytest.mark.gpu
 
 
-def stale_count(one_way: bool, trials: int, default_stream: bool = False, use_graphs: bool = True) -> int:
+def stale_count(one_way: bool, trials: int, default_stream: bool = False, use_graphs: int = True) -> int:
     qe = need_lib()
     d = dev()
     n, k, t = 28672, 4096, 4096
@@ -50,7 +50,7 @@ def stale_count(one_way: bool, trials: int, default_stream: bool = False, use_gr
 
 
 @pytest.mark.parametrize("default_stream", [False, True], ids=["explicit_stream", "default_stream"])
-@pytest.mark.parametrize("use_graphs", [True, False], ids=["graphs", "eager"])
+@pytest.mark.parametrize("use_graphs", [True, False, 2], ids=["graphs", "eager", "executables"])
 def test_two_way_handoff_never_stale(default_stream, use_graphs):
     assert stale_count(one_way=False, trials=30, default_stream=default_stream, use_graphs=use_graphs) == 0
 

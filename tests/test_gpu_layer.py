@@ -189,16 +189,17 @@ def test_split_dw_bitwise_equals_full_backward(case):
     _assert_bitwise(_run_variant(spec, steps, False, False), _run_variant(spec, steps, False, True))
 
 
-def test_graph_replay_bitwise_equals_eager():
+@pytest.mark.parametrize("use_graphs", [1, 2], ids=["launches", "executables"])
+def test_graph_replay_bitwise_equals_eager(use_graphs):
     spec = Spec([(96, 160), (160, 64)], tokens=48, M=8, history=16, margin=0, in_dtype="bf16", shared_view=False,
                 cfg=2)
     steps = [S.ZB_STEP0, S.ZB_STEP1, S.ZB_STEP0]
     eager = _run_variant(spec, steps, False, False)
-    graph = _run_variant(spec, steps, True, False)
+    graph = _run_variant(spec, steps, use_graphs, False)
     _assert_bitwise(eager, graph)
     st = graph[0].ctx.qe_get_state()
     # inputs are uploaded to fresh buffers per action: the buffers are bound into
-    # each action's graph (kernel-node arguments rewritten), with no new capture
+    # each action's graph (its launches' arguments replaced), with no new capture
     assert st["replays"] == sum(len(s) for s in steps) * 2
     assert st["graphs"] > 0 and st["handoffs"] == 2 * st["replays"]
     assert st["captures"] == st["graphs"] and st["rebinds"] > 0
