@@ -6,9 +6,13 @@
 namespace qe {
 
 // What a product costs with each tile shape, in microseconds, fitted to a
-// sweep of 33 products on MI355X (M 64 to 14336, N 152 to 28672, K 128 to
-// 19456, BF16 / FP32 / accumulate outputs; the shape it picks is 3% slower on
-// average than the best one of each product).
+// sweep on MI355X (M 64 to 14336, N 152 to 28672, K 128 to 19456, BF16 / FP32 /
+// accumulate outputs).  Over 34 such products the shape it picks is 2% slower
+// than the best one on average and never slower than a large tile; it is furthest
+// off where several small tiles come close: 2730 x 1365 x 1000 FP32 13.7
+// against 11.6 with 128 x 64 tiles, 320 x 19456 x 1373 19.1 against 16.2 with
+// 128 x 128, 64 x 28672 x 4096 21.4 against 19.8 with 64 x 64
+// (profiles/gemm_tile_choice_34_products.txt has every shape on each).
 //
 // Large tiles run one workgroup per compute unit, round after round: a round
 // of 256 x 256 tiles costs F + T * s, with T = K tiles of 128, s = 1.0 on a
@@ -105,7 +109,7 @@ hipError_t launch_gemm(const GemmParams &g, hipStream_t s, const UpdateParams *f
     return hipSuccess;
   }
   const int force = g_tile_override.load(std::memory_order_relaxed);
-  if (force == kTile256x128 || force >= kTile64x64) return launch_gemm_ring(force, g, s, u);
+  if (force == kTile256x128) return launch_gemm_ring(force, g, s, u);
   if (force > 0) return launch_gemm_large(force, g, s, u);
   const int64_t cus = cu_count();
   const double T = double((g.k + 127) / 128);

@@ -9,6 +9,7 @@ import pytest
 from oracle import fp8, gemm
 from tests.gpu_util import dev, rel_err, torch
 from tests.libqe import need_lib
+from tests.ring_tiles import RING, TAILS
 
 pytestmark = pytest.mark.gpu
 FMTS = {0: "E4M3", 1: "E5M2"}
@@ -223,8 +224,8 @@ def test_forced_tile_shapes_exact(forced_tile, tile, shape):
 
 @pytest.mark.parametrize("shape", [(768, 768, 1000), (1000, 700, 320), (576, 4096, 384), (1024, 1344, 640)], ids=str)
 def test_tile_shapes_same_bits(forced_tile, shape):
-    """Every macro-tile shape (256x256, 256x224, 256x192, 192x256 with four
-    waves, 256x128 with eight) runs the same MFMA with the same reduction bytes per
+    """Every macro-tile shape that can be forced (256x256, 256x224, 256x192,
+    192x256, and 256x128 on the ring kernel) runs the same MFMA with the same reduction bytes per
     lane in the same K order: on random codes (inexact FP32 sums) their outputs
     are bit-identical."""
     qe = forced_tile
@@ -242,9 +243,10 @@ def test_tile_shapes_same_bits(forced_tile, shape):
     for o in outs[1:]:
         np.testing.assert_array_equal(o, outs[0])
 
-# shapes the cost model gives to each small tile (64x64; 128x64 and 64x128 with
-# one and with several workgroups per compute unit; 128x128 likewise), with one
-# to nine K tiles, full and partial last ones, and edges of one row or column
+
+# products of grids that leave the chip idle, with one to twelve K tiles, full
+# and partial last ones, and edges of one row or column (most take 64x64; see
+# RING for a product of every small tile)
 SMALL_TILE_SHAPES = [(1, 1, 1), (65, 63, 129), (64, 64, 512), (129, 200, 1152), (256, 256, 1029), (1000, 1365, 1000),
                      (1365, 1000, 257), (2048, 1030, 768), (1030, 2048, 640), (512, 4096, 1500), (4096, 513, 1408),
                      (2048, 2050, 1152), (1024, 4096, 1100), (2049, 4095, 384)]
@@ -279,6 +281,51 @@ def test_small_tiles_same_bits_as_large(forced_tile, shape):
                 got.append(c.view(torch.int16 if out == qe.BF16 else torch.int32))
             assert torch.equal(got[0], got[1])
             assert torch.equal(got[1][:, n:], c0.view(got[1].dtype)[:, n:])
+
+
+@pytest.mark.parametrize("tile,m,n,loops", RING, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else None)
+def test_every_ring_tile_same_bits_as_large(forced_tile, tile, m, n, loops):
+    """A product of every small tile shape, output and length of the K loop around the ring's (the shape it gets
+    is checked in test_gemm_dispatch.py): the bits of the 256 x 256 tile on random codes, with NaN codes past
+    K, from rows that are vector-aligned and from odd ones one element past any alignment, and not one
+    byte beside them."""
+    qe = forced_tile
+    d = dev()
+    g = torch.Generator(device=d)
+    s = torch.tensor([2.0 ** -2, 2.0 ** 3], dtype=torch.float32, device=d)
+
+    def codes(rows, k, top):  # codes 0 .. top - 1 of either sign are finite
+        c = torch.randint(0, top, (rows, rup16(k)), generator=g, dtype=torch.uint8, device=d)
+        c |= torch.randint(0, 2, c.shape, generator=g, dtype=torch.uint8, device=d) << 7
+        c[:, k:] = 0x7F
+        return c
+
+    for out, tiles in loops.items():
+        dtype, mode = (qe.BF16 if out == "bf16" else qe.F32), (qe.ACCUM if out == "accumulate" else qe.INIT)
+        for t in tiles:
+            for lack in TAILS:
+                k = 128 * t - lack
+                g.manual_seed(k + m)
+                a, b = codes(m, k, 0x40), codes(n, k, 0x7F)  # E5M2 below 2^1, E4M3
+                for shift, ldc in ((0, (n + 3) // 4 * 4), (1, (n + 3) // 4 * 4 + 3)):
+                    c0 = torch.randn(shift + m * ldc + 8, generator=g, device=d) * 100
+                    c0 = c0.to(torch.bfloat16) if out == "bf16" else c0
+                    got = []
+                    for force in (1, 0):
+                        assert qe.qe_set_gemm_tile(force) == "OK"
+                        c = c0.clone()
+                        assert qe.qe_fp8_gemm_tn(a, 1, a.shape[1], b, 0, b.shape[1], m, n, k, s[0:1], s[1:2], c[shift:],
+                                                 dtype, ldc, mode) == "OK"
+                        got.append(c.view(torch.int16 if out == "bf16" else torch.int32))
+                    case = (out, k, shift)
+                    assert torch.equal(got[0], got[1]), case
+                    assert not torch.equal(got[1], c0.view(got[1].dtype)), case
+                    if ldc > n:
+                        beside = got[1][shift:shift + m * ldc].view(m, ldc)[:, n:]
+                        assert torch.equal(beside, c0.view(got[1].dtype)[shift:shift + m * ldc].view(m, ldc)[:, n:]), case
+                    ends = [got[1][:shift], got[1][shift + m * ldc:]]
+                    assert torch.equal(torch.cat(ends), torch.cat([c0.view(got[1].dtype)[:shift],
+                                                                   c0.view(got[1].dtype)[shift + m * ldc:]])), case
 
 
 def _lut_codes(d, seed, rows, cols, lo, hi, fmt):
@@ -446,9 +493,9 @@ def test_seeded_shape_sweep_exact(shape):
                          ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("out", ["f32", "bf16", "accumulate"])
 def test_destination_at_element_alignment(forced_tile, shape, out):
-    """The destination starts one element past every vector alignment and its rows have an odd stride: every
-    tile shape stores the exact integer product (BF16: rounded once), column counts of every remainder by
-    four, and no other element."""
+    """The destination starts one element past every vector alignment and its rows have an odd stride: the tile
+    the cost model picks (64 x 64 here) and every shape that can be forced store the exact integer product (BF16:
+    rounded once), column counts of every remainder by four, and no other element."""
     qe = forced_tile
     d = dev()
     m, n, k = shape
