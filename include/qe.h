@@ -168,16 +168,21 @@ qe_status qe_quantize_fp8_current(const void *in, qe_dtype in_dtype, int64_t row
 /* Allocation-free variant of qe_quantize_fp8_current, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc): the same cast with the same results, but
- * the amax accumulator (the per-line partial maxima the amax pass folds its
- * workgroups into) is a scratch array inside the library, 16 KiB per device
- * and held by each device the library runs on until the process ends,
- * instead of one the caller brings in meta_host->amax_accum, which must be
- * NULL here.  The call allocates nothing (no hipMalloc, hipFree or allocating
- * library routine); the first call on a device looks up that device's copy of
- * the scratch.  Four launches on `stream`: a kernel clears the scratch, then
- * qe_quantize_fp8_current's amax pass, scale update and cast.  The scratch
- * size does not depend on the tensor (any number of workgroups folds into its
- * 64 lines), so every size qe_quantize_fp8_current accepts is accepted.
+ * what the amax pass leaves per workgroup goes into a scratch array inside the
+ * library, 16 KiB per device and held by each device the library runs on until
+ * the process ends, instead of into an accumulator the caller brings in
+ * meta_host->amax_accum, which must be NULL here.  The call allocates nothing
+ * (no hipMalloc, hipFree or allocating library routine); the first call on a
+ * device looks up that device's copy of the scratch.
+ * A non-empty tensor of up to 64 MB (an amax pass of at most 1024 workgroups)
+ * takes two launches on `stream`: the amax pass, which leaves one partial
+ * maximum per workgroup in the scratch, and the cast, which derives the scale
+ * from them and itself writes scale, scale_inv, the cleared amax slot, the
+ * snapshot and the token.  A larger one takes four: a kernel clears the
+ * scratch, then the amax pass (its workgroups fold into 64 lines of the
+ * scratch), the scale update and the cast of qe_quantize_fp8_current; an empty
+ * one takes these without the amax pass.  So every size qe_quantize_fp8_current
+ * accepts is accepted.
  * Every call on one device shares that device's scratch: calls that overlap
  * on one device (on different streams, or from different host threads
  * without ordering) race and give undefined results; calls ordered on one
@@ -209,11 +214,11 @@ qe_status qe_fp8_gemm_tn(const uint8_t *a, qe_fp8_fmt fmt_a, int64_t lda, const 
                          qe_stream stream);
 
 /* Macro-tile shape of every FP8 GEMM the library launches (qe_fp8_gemm_tn and
- * the layer actions).  QE_TILE_AUTO picks, per call, among these shapes and
- * smaller ones (64x64 to 128x128) the one that a measured cost model of rounds
- * of workgroups over the device's compute units (256 on MI355X, read from the
- * device properties) expects to be fastest; the others force one shape (for
- * tests and measurements).  Process-wide; it applies to launches enqueued afterwards
+ * the layer actions).  QE_TILE_AUTO picks, per call, among these shapes but
+ * 256x128, and smaller ones (64x64 to 128x128), the one that a measured cost
+ * model of rounds of workgroups over the device's compute units (256 on MI355X,
+ * read from the device properties) expects to be fastest; the others force one
+ * shape (for tests and measurements).  Process-wide; it applies to launches enqueued afterwards
  * (a graph captured earlier keeps the shapes it was captured with).  The
  * shapes all give the same bits: the same 16x16x128 MFMA with the same
  * reduction bytes per lane, the same order along K, no split reduction.

@@ -42,10 +42,11 @@
 #include "kernels.h"
 
 // Scratch of qe_quantize_fp8_current_noalloc: one amax accumulator
-// (kAmaxLines lines, kAmaxStride floats apart: 16 KiB), one copy per device,
-// held until the process ends.  In host code this name is a host-side stand-in:
+// (kAmaxLines lines, kAmaxStride floats apart: 16 KiB), or the partial maxima
+// of an amax pass; one copy per device, held until the process ends.  In host code this name is a host-side stand-in:
 // the device address comes from hipGetSymbolAddress (noalloc_scratch below).
 static __device__ __align__(256) float scratch[qe::kAmaxLines * qe::kAmaxStride];
+static_assert(qe::kMaxPartials <= qe::kAmaxLines * qe::kAmaxStride, "the partial maxima fit in the scratch");
 
 namespace {
 
