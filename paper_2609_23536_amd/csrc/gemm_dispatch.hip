@@ -8,7 +8,7 @@ namespace qe {
 // What a product costs with each tile shape, in microseconds, fitted to a
 // sweep on MI355X (M 64 to 14336, N 152 to 28672, K 128 to 19456, BF16 / FP32 /
 // accumulate outputs).  Over 34 such products the shape it picks is 2% slower
-// than the best one on average and never slower than a large tile; it is furthest
+// than the best one on average and never slower than 256 x 256; it is furthest
 // off where several small tiles come close: 2730 x 1365 x 1000 FP32 13.7
 // against 11.6 with 128 x 64 tiles, 320 x 19456 x 1373 19.1 against 16.2 with
 // 128 x 128, 64 x 28672 x 4096 21.4 against 19.8 with 64 x 64

@@ -40,9 +40,14 @@ __device__ __forceinline__ v8i mask_frag(v8i f, int valid) {
   return f;
 }
 
+// Two workgroups per compute unit where the LDS holds two.  Their 256 registers
+// per lane then suffice without a spill, the 128 x 128 tile with 224, as long as
+// the compiler is kept from packed FP32 instructions: with them the same source
+// takes 256 and spills 70, and every reload in the K loop would wait for the
+// LDS-bound loads in flight.  test_kernel_resources.py checks the built library.
 template <int FA, int FB, int BM, int BN, int S>
-__global__ __launch_bounds__(256, (BM + BN) * BK * S > 81920 ? 1 : 2) void gemm_tn_ring_kernel(GemmParams g, int tiles_m, int tiles_n, int nt,
-                                                           UpdateParams upd) {
+__global__ __launch_bounds__(256, (BM + BN) * BK * S > 81920 ? 1 : 2) void gemm_tn_ring_kernel(
+    GemmParams g, int tiles_m, int tiles_n, int nt, UpdateParams upd) {
   static_assert(BM % 64 == 0 && BN % 64 == 0 && S >= 2, "tile sizes");
   constexpr int NW = 4, TM = BM / 2, TN = BN / 2;
   constexpr int I = TM / 16, J = TN / 16;
@@ -265,7 +270,8 @@ __global__ __launch_bounds__(256, (BM + BN) * BK * S > 81920 ? 1 : 2) void gemm_
 
   // Epilogue: BM / 64 passes of 64 rows through LDS.  Accumulating, a pass
   // reads its destination before it stages its rows, all loads in flight.
-    // Accesses are non-temporal, as in the large tiles, unless launch_ring says otherwise.
+  // Accesses are non-temporal, as in the large tiles, unless launch_ring says
+  // otherwise.
   const int e = pow2_exponent(g.a_scale_inv) + pow2_exponent(g.b_scale_inv);
   float *ep = reinterpret_cast<float *>(smem);
   constexpr int RW = ER < TM ? ER : TM;  // rows a wave stages per pass
