@@ -8,12 +8,12 @@ master weights, amax history 1024):  F (with the weight-cache refresh, since
 every step follows a version bump), then dI and the deferred dW with direct
 placement into one flat FP32 main-gradient buffer, then arena finalize and
 optimizer commit.  The stage's graphs are captured before the first step
-(qe_prebuild_graphs) and every action replays its graph (chains as short as
-these are replayed launch by launch), by default on the caller's stream
-(stream order gives both directions of the handoff; --executor two-way runs
-the paper's two-way handoff through the library's graph stream instead, and
-the line reports the other executor's step time beside the headline).  Inputs are synthetic, seeded, and resident in HBM
-before timing starts.
+(qe_prebuild_graphs) and every action replays its captured chain (chains as
+short as these launch by launch), by default on the caller's stream (stream
+order gives both directions of the handoff; --executor two-way runs the
+paper's two-way handoff through the library's graph stream instead, and the
+line reports the other executor's step time beside the headline).  Inputs are
+synthetic, seeded, and resident in HBM before timing starts.
 
 Prints one JSON line.  `value` is GEMM FLOPs (fwd + dI + dW, 2*M*N*K each)
 per second over the whole step, quantization and scale updates included.
@@ -22,13 +22,13 @@ carry on the stream the library launches it on, in an instrumented eager pass
 over the same steps.
 `cpu_baseline` times the CPU oracle stage by stage on a bounded sample of the
 same workload.  Beside the headline the line carries the same steps under the
-other executor, with the actions' kernels launched the other way (direct
-launches against graph replay), with copied gradients, with current scaling,
-after a checkpoint restart, and with the caller's buffers rotated every step
-under the three ways a replayed graph meets new buffers; per-action latencies
-of a single small linear; and the deferred dW GEMM alone at the zero-bubble
-microbatch, INIT- and ACCUM-placed.  A progress line after every setup phase
-and every pass goes to stderr.
+other executor, without captured chains ("direct": the same launches, planned
+anew in every call; under --eager with them), with copied gradients, with
+current scaling, after a checkpoint restart, and with the caller's buffers
+rotated every step under the three ways a captured chain meets new buffers;
+per-action latencies of a single small linear; and the deferred dW GEMM alone
+at the zero-bubble microbatch, INIT- and ACCUM-placed.  A progress line after
+every setup phase and every pass goes to stderr.
 """
 from __future__ import annotations
 
@@ -59,7 +59,7 @@ def parse():
     ap.add_argument("--steps", type=int, default=100, help="timed steps (the stage replayed 100 times by default)")
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--workload", default="llama3_70b_stage_8192tok")
-    ap.add_argument("--eager", action="store_true", help="launch kernels directly instead of graph replay")
+    ap.add_argument("--eager", action="store_true", help="plan and launch every call anew instead of replaying captured chains")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-ablation", action="store_true",
                     help="skip the copied-gradient passes (direct placement only)")
@@ -70,8 +70,8 @@ def parse():
                          "two-way: on the library's graph stream behind the paper's two-way handoff")
     ap.add_argument("--no-executor", action="store_true", help="skip the pass with the other executor")
     ap.add_argument("--no-launch-mode", action="store_true",
-                    help="skip the pass that launches the same actions the other way (direct launches under graph "
-                         "replay, graph replay under --eager)")
+                    help="skip the pass that launches the same actions the other way (planned anew in every call, or "
+                         "under --eager replayed from captured chains)")
     ap.add_argument("--no-wgrad", action="store_true",
                     help="skip the dW-placement measurement at the zero-bubble workload's 2048-token microbatch")
     ap.add_argument("--no-latency", action="store_true",
@@ -85,14 +85,26 @@ def parse():
     return ap.parse_args()
 
 
-GEMM_SOURCE = os.path.join(ROOT, "paper_2609_23536_amd", "csrc", "gemm_fp8.hip")
+CSRC = os.path.join(ROOT, "paper_2609_23536_amd", "csrc")
+GEMM_SOURCES = ("gemm_fp8.hip", "gemm_ring.hip", "gemm_dispatch.hip", "gemm_util.h")
+
+
+def gemm_source_sha256(csrc=CSRC):
+    """Of the GEMM's source files without comments and blank space: what was measured on other comments holds."""
+    import hashlib
+    import re
+    h = hashlib.sha256()
+    for name in GEMM_SOURCES:
+        text = open(os.path.join(csrc, name)).read()
+        code = re.sub(r'"(?:\\.|[^"\\])*"|//[^\n]*|/\*.*?\*/', lambda m: m[0] if m[0][0] == '"' else " ", text, flags=re.S)
+        h.update("".join(code.split()).encode() + b"\n")
+    return h.hexdigest()
 
 
 def gemm_traffic_per_launch(workload):
     """HBM bytes per GEMM launch from the committed counter runs on this
-    workload, or None when there are none or they were taken on a different
-    GEMM kernel source than the current one."""
-    import hashlib
+    workload, or None when there are none or they were taken on other GEMM
+    kernel source than the current one."""
     path = os.path.join(ROOT, "profiles", f"gemm_{workload}_traffic.txt")
     if not os.path.exists(path):
         return None
@@ -101,8 +113,7 @@ def gemm_traffic_per_launch(workload):
         if ":" in line and not line.startswith("#"):
             k, v = line.split(":", 1)
             kv[k.strip()] = v.strip()
-    sha = hashlib.sha256(open(GEMM_SOURCE, "rb").read()).hexdigest()
-    if kv.get("kernel_source_sha256") != sha or kv.get("workload") != workload:
+    if kv.get("kernel_source_sha256") != gemm_source_sha256() or kv.get("workload") != workload:
         return None
     return float(kv["gemm_hbm_bytes_per_launch"])
 
@@ -216,11 +227,12 @@ def per_action_latency(qe, torch, device, steps=200, warmup=10):
     """Latency-bound case: one FP8 linear (K = N = 256), two microbatches of 128
     tokens, fp32 inputs, history 4, schedule F0 F1 dI0 dI1 dW0 dW1 (both dW into
     one shared view: INIT, then ACCUM), then finalize and commit.  Mean wall time
-    per action: graph replay and direct launches, each behind the two-way
+    per action: captured chains ("graph", replayed launch by launch at this
+    length) and launches planned in every call ("eager"), each behind the two-way
     handoff (the graph stream) and on the caller's stream; and, on the caller's
     stream, with the caller's X / dY / Y / dX buffers rotated over three sets
-    every step under the three ways a replayed graph can meet new buffers
-    (kernel-node arguments rewritten in place, the paper's static buffers with
+    every step under the three ways a captured chain can meet new buffers
+    (its arguments replaced in place, the paper's static buffers with
     copies, a new capture)."""
     import numpy as np
     import workloads as W
@@ -607,8 +619,8 @@ def main():
         del c
         torch.cuda.empty_cache()
 
-    # the same steps with the actions' kernels launched the other way (direct
-    # launches when the headline replays graphs), on the same executor
+    # the same steps with the actions' launches made the other way (planned in
+    # every call when the headline replays captured chains), on the same executor
     mode_ms = None
     if not args.no_launch_mode:
         c = StageBench(qe, torch, wl, not use_graphs, dev, replay_on_caller=on_caller)
@@ -620,8 +632,8 @@ def main():
         progress("other launch-mode pass")
 
     # the caller's X / dY / Y / dX buffers rotated over three sets every step
-    # (as a training loop hands the layer new tensors): kernel-node arguments
-    # rewritten in place, the paper's static buffers with copies, re-capture
+    # (as a training loop hands the layer new tensors): the chains' arguments
+    # replaced in place, the paper's static buffers with copies, re-capture
     rotation = None
     if use_graphs and not args.no_rotate:
         rotation = {"buffer_sets": 3}
@@ -696,7 +708,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": round(gemm_tflops, 2), "peak": FP8_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(gemm_tflops / FP8_PEAK_TFLOPS, 4),
                      "traffic": gemm_traffic_per_launch(wl.key),
-                     "kernel": "gemm_tn_w4_kernel / gemm_tn_kernel (fwd + dI + dW launches)",
+                     "kernel": "gemm_tn_w4_kernel / gemm_tn_ring_kernel (fwd + dI + dW launches)",
                      "avg_launch_us": round(gemm_ms / gemm_n * 1e3, 2), "launches": gemm_n},
         "quantize": {"achieved": round(q_gbs, 1), "unit": "GB/s", "peak": HBM_PEAK_GBS,
                      "frac": round(q_gbs / HBM_PEAK_GBS, 4), "avg_launch_us": round(q_ms / q_n * 1e3, 2),
