@@ -137,13 +137,13 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
   for (int c = 0; c < CHA; ++c) {
     const int row = 8 * (wave + NW * c) + lrow;
     const int lch = (lane & 7) ^ row_swizzle(row);
-    oa[c] = uint32_t(min(m0 + row, M - 1) * g.lda) + lch * 16;
+    oa[c] = chunk_offset(min(m0 + row, M - 1), g.lda, lch, K);
   }
 #pragma unroll
   for (int c = 0; c < CHB; ++c) {
     const int row = 8 * (wave + NW * c) + lrow;
     const int lch = (lane & 7) ^ row_swizzle(row);
-    ob[c] = uint32_t(min(n0 + row, N - 1) * g.ldb) + lch * 16;
+    ob[c] = chunk_offset(min(n0 + row, N - 1), g.ldb, lch, K);
   }
   const uint32_t lds_base = uint32_t(reinterpret_cast<uintptr_t>(smem));
   const uint32_t wblk = __builtin_amdgcn_readfirstlane(lds_base + uint32_t(wave) * 1024u);
@@ -213,7 +213,8 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(GemmParams g, int tiles
   // tile lands at stage + 4096 d, so M0 steps by a uniform stride, and the
   // step is issued before an MFMA and the load after it (the MFMA is the wait
   // state M0 needs).  Past the last full K tile the loads still run, from
-  // tile 0 into the wave's dummy block with stride 0: no branch per load.
+  // tile 0 into the wave's dummy block with stride 0: no branch per load (and
+  // no byte past a row of less than 128, see chunk_offset).
   auto dma_m0 = [&](int d, uint32_t base, uint32_t stride) {
     if (d == 0)
       asm volatile("s_mov_b32 m0, %0" ::"s"(base) : "m0");

@@ -46,6 +46,16 @@ constexpr int kNT = 2;  // the buffer instructions' nt bit
 // as for a linear 1 KB read (70.7); r >> 1 in its place 74.7, no swizzle 82.7.
 __device__ __forceinline__ int row_swizzle(int r) { return ((r >> 1) & 1) ^ (((r >> 2) & 1) * 4) ^ (((r >> 3) & 1) * 6); }
 
+// Offset of 16-byte chunk `chunk` of operand row `row` in the first K tile.  A
+// reduction shorter than that tile has no chunks past the row's last one: they
+// fall back to it, so that loads of whole tiles issued for their place in the
+// pipeline only (the large tiles issue them past the last full K tile, from the
+// first one) read no byte past the operand, whatever its row stride.
+__host__ __device__ inline uint32_t chunk_offset(int64_t row, int64_t ld, int chunk, int64_t k) {
+  const int last = k >= BK ? BK / 16 - 1 : (k > 0 ? int(k - 1) / 16 : 0);
+  return uint32_t(row * ld) + uint32_t(chunk < last ? chunk : last) * 16u;
+}
+
 __device__ __forceinline__ uint4 mask_tail(uint4 v, int64_t valid) {
   // keep bytes [0, valid), zero the rest; branch-free
   uint32_t w[4] = {v.x, v.y, v.z, v.w};
