@@ -52,6 +52,42 @@ constexpr SmallTile kSmall[] = {
     {kTile128x128, kTile128x128Deep, 128, 128, 4.0, 0.46, 0.0008, 0.52, {2.2, 0.6, 5.6}, 0.8},
 };
 
+// Small tiles in many rounds.  The model above was fitted where the busiest unit
+// has a few small tiles; beyond, it took them for products whose output traffic
+// they cannot keep up with: 4096 x 28672 x 1024 BF16 221 us with 128 x 128 tiles,
+// 118 with 256 x 256; 4096 x 14336 x 512 FP32 99 and 64.  Rows whose pitch is a
+// multiple of 4 KB fall on few memory channels, which costs the short runs of
+// small tiles most (over short K loops, FP32, 128 x 128 tiles take 0.9 of the large
+// tiles' time at other pitches and 1.1 to 1.2 of it there).  So where it
+// picks a small tile for more than kFewTiles per unit, a second model chooses:
+//   t = f + rounds (T (s + k T) + e + [wide pitch] p) + load T q
+// with `load` the tiles per unit and `rounds` that number rounded up; fitted to
+// 1986 such products on MI355X, then adjusted so that the choice costs least.
+// On 410 others it is 3.1% slower than the best shape on average (the first
+// model 9%; profiles/gemm_tile_choice_many_rounds.txt has every shape on a
+// grid of them).  The first model's choice stays for odd rows and, at other
+// pitches, for K up to kShortK, where it is the better one.  Of 900 random
+// products (M, N, K up to 28672) 91 are more than 3% faster so than with the first
+// model alone and 46 slower, and 9 instead of 29 are slower than with large
+// tiles only.
+struct ManyRounds {
+  int tile;
+  int64_t bm, bn;
+  double f, s, q, k;
+  double e[3], p[3];  // by GemmParams::out: FP32, BF16, accumulate
+};
+constexpr int64_t kFewTiles = 2, kShortK = 192, kWidePitch = 4096;  // bytes
+constexpr ManyRounds kManyRounds[] = {
+    {kTile256x256, 256, 256, 1.21, 0.863, 0.437, 0.00293, {10.9, 9.18, 14}, {0.0241, 0.25, 0.954}},
+    {kTile256x224, 256, 224, 3.91, 0.826, 0.783, 0.000663, {6.25, 11.4, 23.8}, {0.514, 0.406, 0.453}},
+    {kTile256x192, 256, 192, 1.62, 0.588, 0.4, 0.00323, {9.93, 9.4, 22.7}, {0.11, 0, 0.281}},
+    {kTile192x256, 192, 256, 2.64, 0.743, 0.475, 0.000228, {7.77, 7.53, 9.06}, {0.0508, 0.401, 0.0188}},
+    {kTile64x64, 64, 64, 1.74, 0.064, 0.0487, 0.00104, {1.16, 1.86, 1.43}, {0.3, 0.0529, 0.369}},
+    {kTile128x64, 128, 64, 1.99, 0.118, 0.0831, 0.00175, {1.7, 2.61, 1.81}, {0.459, 0.465, 0.235}},
+    {kTile64x128, 64, 128, 1.51, 0.126, 0.118, 0.00261, {1.44, 1.83, 1.49}, {0.423, 0.00483, 0.144}},
+    {kTile128x128, 128, 128, 5.01, 0.00963, 0.508, 0.000325, {1.68, 2.28, 7.87}, {0.176, 0.058, 0.671}},
+};
+
 static std::atomic<int> g_tile_override{0};
 
 // Compute units of the current device, read once per device from its properties; 256 on MI355X.
@@ -117,6 +153,7 @@ hipError_t launch_gemm(const GemmParams &g, hipStream_t s, const UpdateParams *f
   const bool scalar = !gemm_vec_ok(g);
   double best = 0.0;
   int pick = 0;
+  int64_t per_unit = 0;  // of a small pick
   auto offer = [&](int tile, double cost) {
     if (pick == 0 || cost < best) {
       best = cost;
@@ -139,8 +176,18 @@ hipError_t launch_gemm(const GemmParams &g, hipStream_t s, const UpdateParams *f
   for (const SmallTile &t : kSmall) {
     const int64_t c = (tiles(t.bm, t.bn) + cus - 1) / cus;
     const bool deep = t.deep != 0 && c == 1;
-    offer(deep ? t.deep : t.tile,
-          t.f + double(c) * (T * (deep ? t.s_deep : t.s + t.s_k * T) + t.e[g.out] + (scalar ? t.scalar : 0.0)));
+    const int tile = deep ? t.deep : t.tile;
+    offer(tile, t.f + double(c) * (T * (deep ? t.s_deep : t.s + t.s_k * T) + t.e[g.out] + (scalar ? t.scalar : 0.0)));
+    if (pick == tile) per_unit = c;
+  }
+  const bool wide_pitch = g.ldc * cbytes % kWidePitch == 0;
+  if (pick >= kTile64x64 && per_unit > kFewTiles && !scalar && (wide_pitch || g.k > kShortK)) {
+    pick = 0;
+    for (const ManyRounds &t : kManyRounds) {
+      const int64_t n = tiles(t.bm, t.bn);
+      const double round = T * (t.s + t.k * T) + t.e[g.out] + (wide_pitch ? t.p[g.out] : 0.0);
+      offer(t.tile, t.f + double((n + cus - 1) / cus) * round + double(n) / double(cus) * T * t.q);
+    }
   }
   return pick >= kTile64x64 ? launch_gemm_ring(pick, g, s, u) : launch_gemm_large(pick, g, s, u);
 }

@@ -29,3 +29,23 @@ def test_products_get_their_small_tile(tile, m, n, loops):
         shape = re.search(r"gemm_tn_ring_kernelILi0ELi0ELi(\d+)ELi(\d+)ELi(\d+)E", name)
         assert shape and tuple(map(int, shape.groups())) == tile, (p, name)
         assert grid == -(-m // bm) * -(-n // bn)
+
+
+# products whose small tiles would run in many rounds, with rows a multiple of 4 KB apart
+MANY_ROUNDS = [(4096, 28672, 1024, BF16), (4096, 28672, 512, "f32"), (8192, 28672, 512, ACCUM), (4096, 14336, 512, "f32"),
+               (4096, 14336, 512, ACCUM), (4096, 4096, 256, BF16), (8192, 8192, 1024, BF16), (4096, 28672, 128, BF16),
+               (28672, 4096, 256, ACCUM)]
+
+
+def test_small_tiles_are_not_taken_for_many_rounds_of_wide_rows():
+    """Large outputs after short reductions, rows a multiple of 4 KB apart: on MI355X small tiles take 1.2 to 1.9
+    times as long there as the large ones."""
+    got = calls(launches, [[*p, p[1]] for p in MANY_ROUNDS])
+    assert all("gemm_tn_w4_kernel" in name for name, _ in got), list(zip(MANY_ROUNDS, got))
+
+
+def test_few_rounds_and_odd_rows_keep_their_small_tiles():
+    """The second rule touches neither products of up to two small tiles per unit nor odd rows."""
+    products = [[512, 4096, 14336, BF16, 4096], [256, 4096, 4096, BF16, 4096], [128, 256, 256, "f32", 256],
+                [1024, 8192, 8192, BF16, 8192], [4100, 4100, 1040, ACCUM, 4103], [1000, 2730, 1365, BF16, 2730]]
+    assert all("gemm_tn_ring_kernel" in name for name, _ in calls(launches, products))
