@@ -55,7 +55,7 @@ constexpr SmallTile kSmall[] = {
 // Small tiles in many rounds.  The model above was fitted where the busiest unit
 // has a few small tiles; beyond, it took them for products whose output traffic
 // they cannot keep up with: 4096 x 28672 x 1024 BF16 221 us with 128 x 128 tiles,
-// 118 with 256 x 256; 4096 x 14336 x 512 FP32 99 and 64.  Rows whose pitch is a
+// 118 with 256 x 256; 8192 x 28672 x 512 FP32 399 and 213.  Rows whose pitch is a
 // multiple of 4 KB fall on few memory channels, which costs the short runs of
 // small tiles most (over short K loops, FP32, 128 x 128 tiles take 0.9 of the large
 // tiles' time at other pitches and 1.1 to 1.2 of it there).  So where it
